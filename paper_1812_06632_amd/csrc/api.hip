@@ -53,7 +53,7 @@ struct soc_ctx_s {
     // scratch
     DevStats *d_stats = nullptr;              // [0] per call, [1] running total
     unsigned long long *d_counter = nullptr;
-    double *d_tmp_out = nullptr;              // small result buffer (temperature stats)
+    double *h_tmp_out = nullptr;              // small result buffer in pinned host memory (temperature stats)
     double *d_priv = nullptr;                 // kPrivCopies private copies of the absorbed array (zero between launches)
     int64_t cap_priv = 0;
     double *d_priv_self = nullptr;            // the same for the ALI self-absorption tally
@@ -136,6 +136,8 @@ struct soc_temp_table_s {
     int32_t nT = 0;
     double T_floor = 0.0, T_max = 0.0, lnTf = 0.0, dlnT = 0.0;
     double *d_lnG = nullptr;
+    double G0 = 0.0, Gn = 0.0, start_scale = 0.0;   // the table's ends; its search (TempArgs)
+    uint16_t *d_start = nullptr;
 };
 
 struct soc_shg_model_s {
@@ -526,7 +528,7 @@ soc_status soc_ctx_create(int32_t hip_device, void *hip_stream, soc_ctx *out)
     c->batch_lds_cells = std::min<int64_t>(c->max_lds_cells, 13824);
     if (hipMalloc((void **)&c->d_stats, 2 * sizeof(DevStats)) != hipSuccess ||
         hipMalloc((void **)&c->d_counter, sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc((void **)&c->d_tmp_out, 8 * sizeof(double)) != hipSuccess) {
+        hipHostMalloc((void **)&c->h_tmp_out, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         soc_ctx_destroy(c);
         return SOC_ENOMEM;
     }
@@ -548,7 +550,7 @@ void soc_ctx_destroy(soc_ctx c)
     for (auto e : c->ev_stop) (void)hipEventDestroy(e);
     (void)hipFree(c->d_stats);
     (void)hipFree(c->d_counter);
-    (void)hipFree(c->d_tmp_out);
+    (void)hipHostFree(c->h_tmp_out);
     (void)hipFree(c->d_priv);
     (void)hipFree(c->d_priv_self);
     (void)hipFree(c->d_peel);
@@ -1316,6 +1318,23 @@ soc_status soc_temp_table_build(soc_ctx c, int32_t K, const double *nu, const do
         if (!std::isfinite(h[j]) || (j > 0 && !(h[j] > h[j - 1])))
             return cleanup(fail(c, SOC_EINVAL, "Gamma(T) is not finite and increasing on [T_floor, T_max] (bin %d)", j));
     }
+    // search starts: the last entry safely below each of kTempStarts equal
+    // steps of ln Gamma (the margins cover the rounding of the edge and of
+    // the device's step number)
+    t->G0 = h.front();
+    t->Gn = h.back();
+    t->start_scale = kTempStarts / (t->Gn - t->G0);
+    std::vector<uint16_t> start(kTempStarts);
+    for (int b = 0, lo = 0; b < kTempStarts; ++b) {
+        const double edge = t->G0 + (b - 1e-9) / t->start_scale - 1e-15 * (std::fabs(t->G0) + std::fabs(t->Gn));
+        while (lo + 2 < nT && h[lo + 1] <= edge) ++lo;
+        start[b] = (uint16_t)lo;
+    }
+    if (hipMalloc((void **)&t->d_start, sizeof(uint16_t) * kTempStarts) != hipSuccess)
+        return cleanup(fail(c, SOC_ENOMEM, "temperature table"));
+    if (hipMemcpyAsync(t->d_start, start.data(), sizeof(uint16_t) * kTempStarts, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+        hipStreamSynchronize(c->stream) != hipSuccess)
+        return cleanup(fail(c, SOC_EHIP, "table upload"));
     *out = t;
     return cleanup(SOC_OK);
 }
@@ -1325,30 +1344,88 @@ void soc_temp_table_destroy(soc_temp_table t)
     if (!t) return;
     (void)hipSetDevice(t->device);
     (void)hipFree(t->d_lnG);
+    (void)hipFree(t->d_start);
     delete t;
 }
 
-// Statistics scratch of the temperature kernels (allocated on first use),
-// with the fine histogram cleared by kernels (no memset nodes in graphs).
+// Statistics scratch of the temperature kernels (allocated and cleared on
+// first use; every call leaves the histograms zero).
 static soc_status temp_stats_buffers(soc_ctx c, TempArgs &a)
 {
     if (!c->d_tpart) {
         if (c->capturing) return fail(c, SOC_ESTATE, "first temperature statistics call inside a graph capture");
-        if (hipMalloc((void **)&c->d_tpart, (size_t)kTempBlocks * 8 * sizeof(double)) != hipSuccess ||
-            hipMalloc((void **)&c->d_thist, (size_t)(kTempBlocks + 1) * kHistBins * sizeof(unsigned int)) != hipSuccess ||
+        double *part = nullptr;
+        if (hipMalloc((void **)&c->d_thist, kHistBins * sizeof(unsigned int)) != hipSuccess ||
             hipMalloc((void **)&c->d_tmeta, 8 * sizeof(double)) != hipSuccess ||
-            hipMalloc((void **)&c->d_tfine_n, kHistBins * sizeof(unsigned int)) != hipSuccess ||
-            hipMalloc((void **)&c->d_tfine_T, kHistBins * sizeof(double)) != hipSuccess)
+            hipMalloc((void **)&c->d_tfine_n, kFineBins * sizeof(unsigned int)) != hipSuccess ||
+            hipMalloc((void **)&c->d_tfine_T, kFineBins * sizeof(double)) != hipSuccess ||
+            hipMalloc((void **)&part, (size_t)kTempBlocks * 8 * sizeof(double)) != hipSuccess) {
+            (void)hipFree(c->d_thist);
+            (void)hipFree(c->d_tmeta);
+            (void)hipFree(c->d_tfine_n);
+            (void)hipFree(c->d_tfine_T);
+            c->d_thist = nullptr;
+            c->d_tmeta = nullptr;
+            c->d_tfine_n = nullptr;
+            c->d_tfine_T = nullptr;
             return fail(c, SOC_ENOMEM, "temperature statistics buffers");
+        }
+        c->d_tpart = part;
+        HIPCHK(c, launch_fill_i32((int32_t *)c->d_thist, 0, kHistBins, c->stream));
+        HIPCHK(c, launch_fill_i32((int32_t *)c->d_tfine_n, 0, kFineBins, c->stream));
+        HIPCHK(c, launch_fill_f64(c->d_tfine_T, 0.0, kFineBins, c->stream));
     }
-    HIPCHK(c, launch_fill_i32((int32_t *)c->d_tfine_n, 0, kHistBins, c->stream));
-    HIPCHK(c, launch_fill_f64(c->d_tfine_T, 0.0, kHistBins, c->stream));
     a.part = c->d_tpart;
-    a.hist_part = c->d_thist;
-    a.hist_total = c->d_thist + (size_t)kTempBlocks * kHistBins;
+    a.hist_total = c->d_thist;
     a.meta = c->d_tmeta;
     a.fine_n = c->d_tfine_n;
     a.fine_T = c->d_tfine_T;
+    return SOC_OK;
+}
+
+// The fields of a temperature pass that the grid and the table give.
+static TempArgs temp_args(const soc_grid g, const soc_temp_table t)
+{
+    TempArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.words = g->d_words;
+    a.ncells = g->ncells;
+    for (int i = 0; i <= kMaxLevels; ++i) a.level_offset[i] = i <= g->nlevels ? g->level_offset[i] : g->ncells;
+    a.nlevels = g->nlevels;
+    a.root_cell_cm = g->root_cell_cm;
+    a.lnG = t->d_lnG;
+    a.nT = t->nT;
+    a.lnTf = t->lnTf;
+    a.dlnT = t->dlnT;
+    a.T_floor = t->T_floor;
+    a.T_max = t->T_max;
+    a.G0 = t->G0;
+    a.Gn = t->Gn;
+    a.start = t->d_start;
+    a.start_scale = t->start_scale;
+    // coarse bins of 2^sh floats, the smallest that span [T_floor, T_max]
+    // (at least 2^kFineBits, so that a bin divides into the fine bins)
+    const float lo = (float)t->T_floor, hi = (float)t->T_max;
+    uint32_t ulo, uhi;
+    std::memcpy(&ulo, &lo, sizeof ulo);
+    std::memcpy(&uhi, &hi, sizeof uhi);
+    a.sh = kFineBits;
+    while (((uhi >> a.sh) - (ulo >> a.sh)) >= (uint32_t)kHistBins) ++a.sh;
+    a.b0 = (ulo >> a.sh) << a.sh;
+    a.blocks = temp_blocks(g->ncells);
+    return a;
+}
+
+// Launch the statistics of a temperature pass and wait for them.
+static soc_status temp_stats(soc_ctx c, const TempArgs &a, soc_temp_stats *stats)
+{
+    HIPCHK(c, launch_temp_stats(a, c->h_tmp_out, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    const double *h = c->h_tmp_out;
+    stats->mean_T = h[0];
+    stats->hot5_mean_T = h[1];
+    stats->mean_rel_change = h[2];
+    stats->clamped = (uint64_t)h[3];
     return SOC_OK;
 }
 
@@ -1380,42 +1457,18 @@ static soc_status update_temperature(soc_ctx c, soc_grid g, soc_temp_table t, co
     if (g->ctx != c || t->ctx != c) return fail(c, SOC_EINVAL, "grid/table belong to another context");
     if (c->capturing && stats) return fail(c, SOC_ESTATE, "statistics not allowed during graph capture");
     HIPCHK(c, hipSetDevice(c->device));
-    TempArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.words = g->d_words;
-    a.ncells = g->ncells;
-    for (int i = 0; i <= kMaxLevels; ++i) a.level_offset[i] = i <= g->nlevels ? g->level_offset[i] : g->ncells;
-    a.nlevels = g->nlevels;
-    a.root_cell_cm = g->root_cell_cm;
-    a.lnG = t->d_lnG;
-    a.nT = t->nT;
-    a.lnTf = t->lnTf;
-    a.dlnT = t->dlnT;
-    a.T_floor = t->T_floor;
-    a.T_max = t->T_max;
+    TempArgs a = temp_args(g, t);
     a.absorbed = d_absorbed;
     a.ali_self = d_self;
     a.ali_emit = d_emitted;
     a.T_old = d_T_old;
     a.T_new = d_T_new;
-    int64_t blocks = (g->ncells + 255) / 256;
-    a.blocks = (int32_t)(blocks < kTempBlocks ? (blocks < 1 ? 1 : blocks) : kTempBlocks);
     if (stats) {
         soc_status st = temp_stats_buffers(c, a);
         if (st != SOC_OK) return st;
     }
     HIPCHK(c, launch_temp_update(a, c->stream));
-    if (stats) {
-        HIPCHK(c, launch_temp_stats(a, c->d_tmp_out, c->stream));
-        double h[4];
-        HIPCHK(c, hipMemcpyAsync(h, c->d_tmp_out, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        stats->mean_T = h[0];
-        stats->hot5_mean_T = h[1];
-        stats->mean_rel_change = h[2];
-        stats->clamped = (uint64_t)h[3];
-    }
-    return SOC_OK;
+    return stats ? temp_stats(c, a, stats) : SOC_OK;
 }
 
 soc_status soc_temperature_stats(soc_ctx c, soc_grid g, soc_temp_table t, const float *d_T, soc_temp_stats *stats)
@@ -1425,32 +1478,14 @@ soc_status soc_temperature_stats(soc_ctx c, soc_grid g, soc_temp_table t, const 
     if (g->ctx != c || t->ctx != c) return fail(c, SOC_EINVAL, "grid/table belong to another context");
     NOT_WHILE_CAPTURING(c);
     HIPCHK(c, hipSetDevice(c->device));
-    TempArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.words = g->d_words;
-    a.ncells = g->ncells;
-    for (int i = 0; i <= kMaxLevels; ++i) a.level_offset[i] = i <= g->nlevels ? g->level_offset[i] : g->ncells;
-    a.nlevels = g->nlevels;
-    a.root_cell_cm = g->root_cell_cm;
-    a.lnG = t->d_lnG;
-    a.nT = t->nT;
-    a.lnTf = t->lnTf;
-    a.dlnT = t->dlnT;
-    a.T_floor = t->T_floor;
-    a.T_max = t->T_max;
+    TempArgs a = temp_args(g, t);
     a.T_new = const_cast<float *>(d_T);   // read only: the kernels never write in this mode
     a.given = 1;
-    const int64_t blocks = (g->ncells + 255) / 256;
-    a.blocks = (int32_t)(blocks < kTempBlocks ? (blocks < 1 ? 1 : blocks) : kTempBlocks);
     soc_status st = temp_stats_buffers(c, a);
     if (st != SOC_OK) return st;
     HIPCHK(c, launch_temp_update(a, c->stream));
-    HIPCHK(c, launch_temp_stats(a, c->d_tmp_out, c->stream));
-    double h[4];
-    HIPCHK(c, hipMemcpyAsync(h, c->d_tmp_out, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    stats->mean_T = h[0];
-    stats->hot5_mean_T = h[1];
+    st = temp_stats(c, a, stats);
+    if (st != SOC_OK) return st;
     stats->mean_rel_change = 0.0;
     stats->clamped = 0;
     return SOC_OK;

@@ -257,6 +257,11 @@ struct TempArgs {
     const double *lnG;
     int32_t nT;
     double lnTf, dlnT, T_floor, T_max;
+    double G0, Gn;               // the table's ends, lnG[0] and lnG[nT - 1]
+    const uint16_t *start;       // kTempStarts start indices into lnG, one per equal step of ln Gamma
+    double start_scale;          // steps per unit of ln Gamma
+    uint32_t b0;                 // histogram: bit pattern of the lowest bin's first float
+    int32_t sh;                  //            and floats per bin (2^sh)
     const double *absorbed;
     const double *ali_self;      // diagonal ALI (NULL = off): self-absorbed and emitted dust energy
     const double *ali_emit;
@@ -266,10 +271,9 @@ struct TempArgs {
     int32_t blocks;              // workgroups of the update and refine passes
     // statistics (part == NULL: not requested)
     double *part;                // blocks x 8 partial sums
-    unsigned int *hist_part;     // blocks x kHistBins coarse ln T histograms
-    unsigned int *hist_total;    // kHistBins
+    unsigned int *hist_total;    // kHistBins coarse temperature bins (zero between calls)
     double *meta;                // 8 values, see temp_stats_reduce_kernel
-    unsigned int *fine_n;        // kHistBins fine bins inside the threshold bin
+    unsigned int *fine_n;        // kFineBins fine bins inside the threshold bin (zero between calls)
     double *fine_T;
 };
 // Learned starting temperatures (surrogate.hip): regular cubic grids of n^3
@@ -304,10 +308,15 @@ hipError_t launch_sur_features(const SurFeatArgs &a, hipStream_t s);
 hipError_t launch_sur_target(const SurMapArgs &a, hipStream_t s);
 hipError_t launch_sur_apply(const SurMapArgs &a, hipStream_t s);
 
+constexpr int kTempMaxT = 4096;    // entries of a temperature table at most
+constexpr int kTempStarts = 4096;  // start indices of its search
 constexpr int kHistBins = 4096;
+constexpr int kFineBits = 13;
+constexpr int kFineBins = 1 << kFineBits;
 constexpr int kTempBlocks = 512;
+int32_t temp_blocks(int64_t ncells);   // workgroups of the update and refine passes
 hipError_t launch_temp_update(const TempArgs &a, hipStream_t s);
-// Hottest-5% statistics after launch_temp_update (fine_n / fine_T zeroed).
+// Hottest-5% statistics after launch_temp_update.
 hipError_t launch_temp_stats(const TempArgs &a, double *out4, hipStream_t s);
 
 // ---- batched launch: many (model, frequency) pairs in one persistent launch

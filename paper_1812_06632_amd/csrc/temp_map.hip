@@ -4,10 +4,9 @@
 // maps from that solution).
 //
 // Temperature: Gamma(T) = 4 pi sum_k w_k sigma_abs,k B_nu_k(T) is tabulated
-// once on a log-T grid; each cell inverts ln Gamma -> ln T by binary search
-// in the table (staged in LDS) and linear interpolation in the log-log
-// plane.  The pass is a streaming pass over the cells (A: 8 B, word: 4 B,
-// T_old: 4 B, T_new: 4 B), bound by HBM bandwidth.
+// once on a log-T grid; each cell inverts ln Gamma -> ln T by a search in
+// the table and linear interpolation in the log-log plane.  The pass streams
+// over the cells (A: 8 B, word: 4 B, T_old: 4 B, T_new: 4 B).
 #include <hip/hip_runtime.h>
 
 #include "soc_kernels.h"
@@ -49,34 +48,70 @@ __device__ inline int level_index(int64_t c, const int64_t *lo, int32_t nlevels)
     return L;
 }
 
-constexpr int kTempThreads = 256;
+// 512-lane workgroups, two per compute unit: 16 waves per CU hide the
+// chains of FP64 divisions, logarithm and exponential of a cell (256 lanes,
+// 8 waves per CU: 56 us for the update pass at 128^3).
+constexpr int kTempThreads = 512;
 
-__device__ inline int coarse_bin(double lnT, double lnTf, double scale)
+// Histogram key of a temperature.  The bit pattern of a float >= 0 grows
+// with its value, so a coarse bin is a range of 2^sh consecutive floats
+// counted from bit pattern b0 (2^sh-aligned, so that a bin never spans two
+// exponents) and the fine bins divide it evenly: no logarithm is taken.
+// Values outside the table's range fall into the end bins.
+__device__ inline int coarse_bin(float T, uint32_t b0, int sh)
 {
-    int b = (int)((lnT - lnTf) * scale);
-    return b < 0 ? 0 : (b >= kHistBins ? kHistBins - 1 : b);
+    const uint32_t u = __float_as_uint(fmaxf(T, 0.0f));
+    const uint32_t b = u > b0 ? (u - b0) >> sh : 0u;
+    return b >= (uint32_t)kHistBins ? kHistBins - 1 : (int)b;
+}
+__device__ inline int fine_bin(float T, int tb, uint32_t b0, int sh)
+{
+    const uint32_t u = __float_as_uint(fmaxf(T, 0.0f)), lo = b0 + ((uint32_t)tb << sh);
+    const uint32_t b = u > lo ? (u - lo) >> (sh - kFineBits) : 0u;
+    return b >= (uint32_t)kFineBins ? kFineBins - 1 : (int)b;
+}
+
+// Sum over the wave, in every lane; fixed order.
+__device__ inline double wave_sum(double v)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
 }
 
 // Temperature of every leaf (given: T_new already holds the temperatures
-// and only the statistics are taken).  With statistics requested, each workgroup
-// also writes its partial sums (count, sum T, sum |dT|/T_old, count with
-// T_old > 0, clamped) and its histogram of ln T over kHistBins coarse bins
-// (privatised in LDS) to its own row -- no global atomics, so the result
-// is deterministic.
+// and only the statistics are taken).  With statistics requested, each
+// workgroup writes its partial sums (count, sum T, sum |dT|/T_old, count with
+// T_old > 0, clamped) to its own row and adds its LDS histogram of the
+// temperatures to the total, whose integer adds give the same result in any
+// order.
+//
+// Bound: FP64 arithmetic (about 250 vector instructions per cell: three
+// divisions, a logarithm, an exponential) next to 20 bytes per cell.  The
+// table's interval is found through a start index per equal step of
+// ln Gamma (one or two table reads instead of a 12-step binary search).
+// Staged: the table and its start indices are copied to LDS, worth it once
+// a lane has several cells; a small grid reads them through L2.
+// A solve with statistics of 128^3 cells: 66 us (with the passes below and
+// the wait for the result; 421 us with logarithmic bins, one histogram row
+// per workgroup and serial sums over the rows).
+template <bool Staged>
 __global__ __launch_bounds__(kTempThreads) void temp_update_kernel(TempArgs a)
 {
-    extern __shared__ double lds_lnG[];
+    __shared__ double sh_lnG[Staged ? kTempMaxT : 1];
+    __shared__ uint16_t sh_start[Staged ? kTempStarts : 1];
     __shared__ unsigned int sh_hist[kHistBins];
     __shared__ double sh_red[kTempThreads / 64][5];
     const bool want = a.part != nullptr;
-    for (int j = threadIdx.x; j < a.nT; j += blockDim.x) lds_lnG[j] = a.lnG[j];
+    if (Staged && !a.given) {
+        for (int j = threadIdx.x; j < a.nT; j += kTempThreads) sh_lnG[j] = a.lnG[j];
+        for (int j = threadIdx.x; j < kTempStarts; j += kTempThreads) sh_start[j] = a.start[j];
+    }
     if (want)
-        for (int j = threadIdx.x; j < kHistBins; j += blockDim.x) sh_hist[j] = 0u;
+        for (int j = threadIdx.x; j < kHistBins; j += kTempThreads) sh_hist[j] = 0u;
     __syncthreads();
-    const double G0 = lds_lnG[0], Gn = lds_lnG[a.nT - 1];
     double cnt = 0.0, sumT = 0.0, sumrel = 0.0, nrel = 0.0, ncl = 0.0;
-    const double hist_scale = (double)kHistBins / ((a.nT - 1) * a.dlnT);
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.ncells; c += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t c = (int64_t)blockIdx.x * kTempThreads + threadIdx.x; c < a.ncells; c += (int64_t)gridDim.x * kTempThreads) {
         const uint32_t w = a.words[c];
         const float nf = __uint_as_float(w);
         float Tout = 0.0f;
@@ -102,19 +137,23 @@ __global__ __launch_bounds__(kTempThreads) void temp_update_kernel(TempArgs a)
                     clamped = true;
                 } else {
                     const double ly = log(y);
-                    if (!(ly > G0)) {
+                    if (!(ly > a.G0)) {
                         T = a.T_floor;
                         clamped = true;
-                    } else if (ly >= Gn) {
+                    } else if (ly >= a.Gn) {
                         T = a.T_max;
                         clamped = true;
                     } else {
-                        int lo = 0, hi = a.nT - 1;   // lnG[lo] < ly < lnG[hi]
-                        while (hi - lo > 1) {
-                            const int mid = (lo + hi) >> 1;
-                            if (lds_lnG[mid] <= ly) lo = mid; else hi = mid;
+                        // lnG[lo] <= ly < lnG[lo + 1]; the start index is at or below lo
+                        const int b = min((int)((ly - a.G0) * a.start_scale), kTempStarts - 1);
+                        int lo = Staged ? sh_start[b] : a.start[b];
+                        double g0 = Staged ? sh_lnG[lo] : a.lnG[lo], g1 = Staged ? sh_lnG[lo + 1] : a.lnG[lo + 1];
+                        while (g1 <= ly) {
+                            ++lo;
+                            g0 = g1;
+                            g1 = Staged ? sh_lnG[lo + 1] : a.lnG[lo + 1];
                         }
-                        const double t = (ly - lds_lnG[lo]) / (lds_lnG[hi] - lds_lnG[lo]);
+                        const double t = (ly - g0) / (g1 - g0);
                         T = exp(a.lnTf + a.dlnT * ((double)lo + t));
                     }
                 }
@@ -132,19 +171,17 @@ __global__ __launch_bounds__(kTempThreads) void temp_update_kernel(TempArgs a)
                         nrel += 1.0;
                     }
                 }
-                atomicAdd(&sh_hist[coarse_bin(log(fmax(Tf, 1e-30)), a.lnTf, hist_scale)], 1u);
+                atomicAdd(&sh_hist[coarse_bin(Tout, a.b0, a.sh)], 1u);
             }
         }
         if (!a.given) a.T_new[c] = Tout;
     }
     if (!want) return;
-    for (int o = 32; o >= 1; o >>= 1) {
-        cnt += __shfl_xor(cnt, o, 64);
-        sumT += __shfl_xor(sumT, o, 64);
-        sumrel += __shfl_xor(sumrel, o, 64);
-        nrel += __shfl_xor(nrel, o, 64);
-        ncl += __shfl_xor(ncl, o, 64);
-    }
+    cnt = wave_sum(cnt);
+    sumT = wave_sum(sumT);
+    sumrel = wave_sum(sumrel);
+    nrel = wave_sum(nrel);
+    ncl = wave_sum(ncl);
     const int wv = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         sh_red[wv][0] = cnt;
@@ -159,52 +196,96 @@ __global__ __launch_bounds__(kTempThreads) void temp_update_kernel(TempArgs a)
         for (int k = 0; k < kTempThreads / 64; ++k) v += sh_red[k][threadIdx.x];
         a.part[(int64_t)blockIdx.x * 8 + threadIdx.x] = v;
     }
-    for (int j = threadIdx.x; j < kHistBins; j += blockDim.x) a.hist_part[(int64_t)blockIdx.x * kHistBins + j] = sh_hist[j];
+    for (int j = threadIdx.x; j < kHistBins; j += kTempThreads)
+        if (sh_hist[j]) atomicAdd(&a.hist_total[j], sh_hist[j]);
 }
 
 hipError_t launch_temp_update(const TempArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(temp_update_kernel, dim3((unsigned)a.blocks), dim3(kTempThreads), sizeof(double) * a.nT, s, a);
+    if (a.given || a.ncells < 4ll * kTempThreads * a.blocks)
+        hipLaunchKernelGGL(temp_update_kernel<false>, dim3((unsigned)a.blocks), dim3(kTempThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(temp_update_kernel<true>, dim3((unsigned)a.blocks), dim3(kTempThreads), 0, s, a);
     return hipGetLastError();
 }
 
-// Reduce the per-workgroup partial sums and histograms, then locate the
-// coarse bin holding the k-th hottest leaf (k = ceil(0.05 n)).
+int32_t temp_blocks(int64_t ncells)
+{
+    const int64_t b = (ncells + kTempThreads - 1) / kTempThreads;
+    return (int32_t)(b < 1 ? 1 : (b < kTempBlocks ? b : kTempBlocks));
+}
+
+// One workgroup's inclusive scan of one value per lane over 1024 lanes:
+// within each wave by shuffles, then over the 16 wave totals.
+constexpr int kFinThreads = 1024;
+
+__device__ inline double block_scan(double v, double *sh)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
+    if (lane == 63) sh[wv] = v;
+    __syncthreads();
+    double base = 0.0;
+    for (int k = 0; k < wv; ++k) base += sh[k];
+    __syncthreads();
+    return base + v;
+}
+
+// Sum over the workgroups' rows of columns col .. col + n - 1 of `part`
+// (at most 512 rows): result in sh_p of every lane, fixed order.
+template <int N>
+__device__ inline void sum_parts(const TempArgs &a, int col, double (*sh)[8], double *sh_p)
+{
+    const int t = threadIdx.x, wv = t >> 6;
+    double v[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        v[q] = t < a.blocks ? a.part[(int64_t)t * 8 + col + q] : 0.0;
+        v[q] = wave_sum(v[q]);
+        if ((t & 63) == 0) sh[wv][q] = v[q];
+    }
+    __syncthreads();
+    if (t < N) {
+        double s = 0.0;
+        for (int k = 0; k < kFinThreads / 64; ++k) s += sh[k][t];
+        sh_p[t] = s;
+    }
+    __syncthreads();
+}
+
+// Reduce the per-workgroup partial sums, then locate the coarse bin holding
+// the k-th hottest leaf (k = ceil(0.05 n)).  One workgroup; the sums over
+// the rows and the scan over the bins are a few shuffles each (serial loops
+// over 512 rows took 79 us here and 105 us in the finish).
 // meta: [0] count [1] sum T [2] sum rel [3] n rel [4] clamped
 //       [5] threshold bin [6] cells still needed from that bin [7] k
-constexpr int kFinThreads = 1024;
 constexpr int kFinPer = kHistBins / kFinThreads;
 
 __global__ __launch_bounds__(kFinThreads) void temp_stats_reduce_kernel(TempArgs a)
 {
-    __shared__ double sh_n[kFinThreads];
+    __shared__ double sh[kFinThreads / 64][8];
     __shared__ double sh_p[8];
+    __shared__ double sh_s[kFinThreads / 64];
     const int t = threadIdx.x;
-    if (t < 5) {
-        double v = 0.0;
-        for (int b = 0; b < a.blocks; ++b) v += a.part[(int64_t)b * 8 + t];
-        sh_p[t] = v;
-    }
-    // chunk t covers bins [hi - per, hi), counted from the top
+    sum_parts<5>(a, 0, sh, sh_p);
+    // lane t covers bins [hi - per, hi), counted from the top
     const int hi = kHistBins - t * kFinPer;
     double loc[kFinPer];
     double n = 0.0;
     for (int q = 0; q < kFinPer; ++q) {
         loc[q] = (double)a.hist_total[hi - 1 - q];
+        a.hist_total[hi - 1 - q] = 0u;   // left zero for the next call
         n += loc[q];
     }
-    sh_n[t] = n;
-    __syncthreads();
-    for (int o = 1; o < kFinThreads; o <<= 1) {
-        const double add = t >= o ? sh_n[t - o] : 0.0;
-        __syncthreads();
-        sh_n[t] += add;
-        __syncthreads();
-    }
+    const double upto = block_scan(n, sh_s);
     const double count = sh_p[0];
     const double k = ceil(0.05 * count);
-    const double before = t > 0 ? sh_n[t - 1] : 0.0;
-    if (count > 0.0 && before < k && sh_n[t] >= k) {
+    const double before = upto - n;
+    if (count > 0.0 && before < k && upto >= k) {
         double cn = before;
         for (int q = 0; q < kFinPer; ++q) {
             if (cn + loc[q] >= k) {
@@ -232,26 +313,21 @@ __global__ __launch_bounds__(kTempThreads) void temp_stats_refine_kernel(TempArg
 {
     __shared__ double sh[kTempThreads / 64];
     const int tb = (int)a.meta[5];
-    const double hist_scale = (double)kHistBins / ((a.nT - 1) * a.dlnT);
-    const double lo_b = a.lnTf + (double)tb / hist_scale;
-    const double fine_scale = hist_scale * (double)kHistBins;
     double above = 0.0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.ncells; c += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t c = (int64_t)blockIdx.x * kTempThreads + threadIdx.x; c < a.ncells; c += (int64_t)gridDim.x * kTempThreads) {
         const uint32_t w = a.words[c];
+        const float T = a.T_new[c];
         if ((int32_t)w < 0 || !(__uint_as_float(w) > 0.0f)) continue;
-        const double Tf = (double)a.T_new[c];
-        const double lt = log(fmax(Tf, 1e-30));   // a given field may hold zeros
-        const int b = coarse_bin(lt, a.lnTf, hist_scale);
+        const int b = coarse_bin(T, a.b0, a.sh);
         if (b > tb) {
-            above += Tf;
+            above += (double)T;
         } else if (b == tb) {
-            int f = (int)((lt - lo_b) * fine_scale);
-            f = f < 0 ? 0 : (f >= kHistBins ? kHistBins - 1 : f);
+            const int f = fine_bin(T, tb, a.b0, a.sh);
             atomicAdd(&a.fine_n[f], 1u);
-            unsafeAtomicAdd(&a.fine_T[f], Tf);
+            unsafeAtomicAdd(&a.fine_T[f], (double)T);
         }
     }
-    for (int o = 32; o >= 1; o >>= 1) above += __shfl_xor(above, o, 64);
+    above = wave_sum(above);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = above;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -262,76 +338,59 @@ __global__ __launch_bounds__(kTempThreads) void temp_stats_refine_kernel(TempArg
 }
 
 // Final statistics: mean T, hottest-5% mean (cells above the threshold bin
-// plus the hottest cells inside it, resolved on the fine histogram whose
-// bins are 2^-24 of the ln T range wide), mean relative change, clamps.
+// plus the hottest cells inside it, resolved on the fine histogram, whose
+// bins hold a few neighbouring floats), mean relative change, clamps.
+// `out` is pinned host memory: the result needs no copy.
+constexpr int kFinePer = kFineBins / kFinThreads;
+
 __global__ __launch_bounds__(kFinThreads) void temp_stats_finish_kernel(TempArgs a, double *out)
 {
-    __shared__ double sh_n[kFinThreads];
-    __shared__ double sh_T[kFinThreads];
-    __shared__ double sh_above;
+    __shared__ double sh[kFinThreads / 64][8];
+    __shared__ double sh_p[8];
+    __shared__ double sh_s[kFinThreads / 64];
     const int t = threadIdx.x;
-    if (t == 0) {
-        double v = 0.0;
-        for (int b = 0; b < a.blocks; ++b) v += a.part[(int64_t)b * 8 + 5];
-        sh_above = v;
-    }
-    const int hi = kHistBins - t * kFinPer;
+    sum_parts<1>(a, 5, sh, sh_p);
+    const double above = sh_p[0];
+    const int hi = kFineBins - t * kFinePer;
+    double bn[kFinePer], bT[kFinePer];
     double n = 0.0, sT = 0.0;
-    for (int b = hi - 1; b >= hi - kFinPer; --b) {
-        n += (double)a.fine_n[b];
-        sT += a.fine_T[b];
+    for (int q = 0; q < kFinePer; ++q) {
+        const int b = hi - 1 - q;
+        bn[q] = (double)a.fine_n[b];
+        bT[q] = a.fine_T[b];
+        a.fine_n[b] = 0u;   // left zero for the next call
+        a.fine_T[b] = 0.0;
+        n += bn[q];
+        sT += bT[q];
     }
-    sh_n[t] = n;
-    sh_T[t] = sT;
-    __syncthreads();
-    for (int o = 1; o < kFinThreads; o <<= 1) {
-        const double an = t >= o ? sh_n[t - o] : 0.0;
-        const double aT = t >= o ? sh_T[t - o] : 0.0;
-        __syncthreads();
-        sh_n[t] += an;
-        sh_T[t] += aT;
-        __syncthreads();
-    }
+    const double upto_n = block_scan(n, sh_s), upto_T = block_scan(sT, sh_s);
     const double count = a.meta[0];
     const double need = a.meta[6];
     const double k = a.meta[7];
-    const double before_n = t > 0 ? sh_n[t - 1] : 0.0;
-    const double before_T = t > 0 ? sh_T[t - 1] : 0.0;
-    if (count > 0.0 && need > 0.0 && before_n < need && sh_n[t] >= need) {
-        double cn = before_n, cT = before_T;
-        for (int b = hi - 1; b >= hi - kFinPer; --b) {
-            const double bn = (double)a.fine_n[b];
-            if (cn + bn >= need) {
-                cT += (need - cn) * (a.fine_T[b] / bn);
+    const double before_n = upto_n - n;
+    if (count > 0.0 && need > 0.0 && before_n < need && upto_n >= need) {
+        double cn = before_n, cT = upto_T - sT;
+        for (int q = 0; q < kFinePer; ++q) {
+            if (cn + bn[q] >= need) {
+                cT += (need - cn) * (bT[q] / bn[q]);
                 break;
             }
-            cn += bn;
-            cT += a.fine_T[b];
+            cn += bn[q];
+            cT += bT[q];
         }
-        out[1] = (sh_above + cT) / k;
+        out[1] = (above + cT) / k;
     }
     if (t == 0) {
         out[0] = count > 0.0 ? a.meta[1] / count : 0.0;
         out[2] = a.meta[3] > 0.0 ? a.meta[2] / a.meta[3] : __builtin_nan("");
         out[3] = a.meta[4];
         if (!(count > 0.0)) out[1] = 0.0;
-        else if (!(need > 0.0)) out[1] = sh_above / k;
+        else if (!(need > 0.0)) out[1] = above / k;
     }
-}
-
-// Sum of the per-workgroup histograms, one bin per thread (coalesced).
-__global__ __launch_bounds__(256) void temp_hist_reduce_kernel(TempArgs a)
-{
-    const int bin = blockIdx.x * blockDim.x + threadIdx.x;
-    if (bin >= kHistBins) return;
-    unsigned int sum = 0;
-    for (int b = 0; b < a.blocks; ++b) sum += a.hist_part[(int64_t)b * kHistBins + bin];
-    a.hist_total[bin] = sum;
 }
 
 hipError_t launch_temp_stats(const TempArgs &a, double *out4, hipStream_t s)
 {
-    hipLaunchKernelGGL(temp_hist_reduce_kernel, dim3(kHistBins / 256), dim3(256), 0, s, a);
     hipLaunchKernelGGL(temp_stats_reduce_kernel, dim3(1), dim3(kFinThreads), 0, s, a);
     hipLaunchKernelGGL(temp_stats_refine_kernel, dim3((unsigned)a.blocks), dim3(kTempThreads), 0, s, a);
     hipLaunchKernelGGL(temp_stats_finish_kernel, dim3(1), dim3(kFinThreads), 0, s, a, out4);
