@@ -82,7 +82,8 @@ typedef enum {
                                     often share one memory-side transaction.  Batches created while it is
                                     1 also tally their tiled arrays in a brick-ordered scratch [1] */
     SOC_OPT_CHUNK = 8,           /* package ids a wave takes from the global counter at a time, 64..65536
-                                    (smaller: finer load balance between waves) [256] */
+                                    (smaller: finer load balance between waves); launches with fewer ids
+                                    per wave use smaller chunks, down to 64 [256] */
     SOC_OPT_BATCH_LDS_CELLS = 9, /* batches created afterwards: pairs whose grid has at most this many cells
                                     are taken whole by one workgroup, which keeps the grid's absorbed array
                                     in LDS (0 = never; at most what the device's LDS per workgroup holds)

@@ -51,7 +51,7 @@ struct soc_ctx_s {
     int64_t max_lds_cells = 0;        // the most the device's LDS per workgroup holds
     int64_t lds_per_cu = 65536;       // bytes of LDS per compute unit
     // scratch
-    DevStats *d_stats = nullptr;              // [0] per call, [1] running total
+    DevStats *d_stats = nullptr;              // kStatSlots of the call, then kStatSlots of the running total
     unsigned long long *d_counter = nullptr;
     double *h_tmp_out = nullptr;              // small result buffer in pinned host memory (temperature stats)
     double *d_priv = nullptr;                 // kPrivCopies private copies of the absorbed array (zero between launches)
@@ -243,8 +243,8 @@ double dust_offset(uint64_t seed, uint32_t iteration, uint32_t freq_index)
 constexpr int64_t kNaMaxCells = 32768;           // 32^3 cells, every level included
 constexpr int64_t kNaMaxDust = int64_t(1) << 20; // weighted dust packages per call
 constexpr size_t na_round(size_t b) { return (b + 255) & ~size_t(255); }
-constexpr size_t kNaStats = 0;                                              // 2 DevStats
-constexpr size_t kNaCounter = kNaStats + na_round(2 * sizeof(DevStats));    // refill counter
+constexpr size_t kNaStats = 0;                                              // the call's statistics
+constexpr size_t kNaCounter = kNaStats + na_round(kStatSlots * sizeof(DevStats));    // refill counter
 constexpr size_t kNaS = kNaCounter + 256;                                   // capped dust total
 constexpr size_t kNaL = kNaS + 256;
 constexpr size_t kNaA = kNaL + na_round(sizeof(double) * kNaMaxCells);
@@ -274,10 +274,23 @@ soc_status take(soc_ctx c, const ScratchSrc &src, T **ctx_p, int64_t &ctx_cap, i
     return SOC_OK;
 }
 
-// Per-frequency argument block shared by the production and trace kernels.
+// Package ids a wave takes at a time: SOC_OPT_CHUNK at most, and no more
+// than an even share of the frequency's packages over the launch's waves
+// that visit it (all of them, or 1 / K where K frequencies share a launch),
+// but at least the 64 that one grant has to cover.  20000 packages in
+// chunks of 256 kept 78 of 3072 waves busy: 250 us, 140 us in chunks of 64.
+// A share of a quarter or a sixteenth measures the same.
+int32_t chunk_for(soc_ctx c, uint64_t n_total, int32_t K)
+{
+    const uint64_t waves = (uint64_t)(c->num_cus * c->blocks_per_cu * (c->block / 64));
+    return (int32_t)std::max<uint64_t>(64, std::min<uint64_t>((uint64_t)c->chunk, n_total * K / waves));
+}
+
+// Per-frequency argument block shared by the production and trace kernels
+// (K: frequencies in the launch).
 soc_status prepare(soc_ctx c, soc_grid g, const soc_freq *f, const soc_sources *s, uint64_t seed,
                    uint32_t iteration, uint32_t freq_index, double *d_absorbed, McArgs &A,
-                   const ScratchSrc &src = ScratchSrc())
+                   const ScratchSrc &src = ScratchSrc(), int32_t K = 1)
 {
     soc_status st = check_freq(c, f);
     if (st) return st;
@@ -442,23 +455,31 @@ soc_status prepare(soc_ctx c, soc_grid g, const soc_freq *f, const soc_sources *
     }
     A.next_id = src.base ? (unsigned long long *)(src.base + kNaCounter) : c->d_counter;
     A.st_call = src.base ? (DevStats *)(src.base + kNaStats) : c->d_stats;
-    A.st_total = c->d_stats + 1;
+    A.st_total = c->d_stats + kStatSlots;
     A.refill_min = (int32_t)c->refill_min;
     A.inner_steps = (int32_t)c->inner_steps;
-    A.chunk = (int32_t)c->chunk;
+    A.chunk = chunk_for(c, A.n_total, K);
     A.scatter_min = (int32_t)c->scatter_min;
     return SOC_OK;
 }
 
-void to_public(const DevStats &d, soc_sim_stats *o)
+// Wait for the stream and add up one set of statistics slots.
+soc_status read_slots(soc_ctx c, const DevStats *d, soc_sim_stats *o)
 {
-    o->packages = d.packages;
-    o->cell_steps = d.steps;
-    o->scatterings = d.scatterings;
-    o->runaways = d.runaways;
-    o->e_emitted = d.emitted;
-    o->e_absorbed = d.absorbed;
-    o->e_escaped = d.escaped;
+    DevStats h[kStatSlots];
+    HIPCHK(c, hipMemcpyAsync(h, d, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    std::memset(o, 0, sizeof *o);
+    for (const DevStats &s : h) {
+        o->packages += s.packages;
+        o->cell_steps += s.steps;
+        o->scatterings += s.scatterings;
+        o->runaways += s.runaways;
+        o->e_emitted += s.emitted;
+        o->e_absorbed += s.absorbed;
+        o->e_escaped += s.escaped;
+    }
+    return SOC_OK;
 }
 
 }  // namespace
@@ -526,13 +547,13 @@ soc_status soc_ctx_create(int32_t hip_device, void *hip_stream, soc_ctx *out)
         lds_cu > 0)
         c->lds_per_cu = lds_cu;
     c->batch_lds_cells = std::min<int64_t>(c->max_lds_cells, 13824);
-    if (hipMalloc((void **)&c->d_stats, 2 * sizeof(DevStats)) != hipSuccess ||
+    if (hipMalloc((void **)&c->d_stats, 2 * kStatSlots * sizeof(DevStats)) != hipSuccess ||
         hipMalloc((void **)&c->d_counter, sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc((void **)&c->h_tmp_out, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         soc_ctx_destroy(c);
         return SOC_ENOMEM;
     }
-    if (launch_fill_u64((unsigned long long *)c->d_stats, 0ull, 2 * (int64_t)(sizeof(DevStats) / 8), c->stream) != hipSuccess ||
+    if (launch_fill_u64((unsigned long long *)c->d_stats, 0ull, 2 * kStatWords, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
         soc_ctx_destroy(c);
         return SOC_EHIP;
@@ -814,8 +835,7 @@ soc_status soc_simulate_frequency(soc_ctx c, soc_grid g, const soc_freq *f, cons
             A.priv_self = c->d_priv_self;
         }
     }
-    HIPCHK(c, launch_fill_u64((unsigned long long *)c->d_stats, 0ull, (int64_t)(sizeof(DevStats) / 8), c->stream));
-    HIPCHK(c, launch_fill_u64(c->d_counter, 0ull, 1, c->stream));
+    HIPCHK(c, launch_clear2((unsigned long long *)c->d_stats, kStatWords, c->d_counter, 1, c->stream));
     const int blocks = (int)(c->num_cus * c->blocks_per_cu);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
@@ -833,10 +853,7 @@ soc_status soc_simulate_frequency(soc_ctx c, soc_grid g, const soc_freq *f, cons
     if (A.priv_self)
         HIPCHK(c, launch_fold_copies(A.ali_self, A.priv_self, g->ncells, A.brick, g->nx, g->ny, g->nroot, c->stream));
     if (stats) {
-        DevStats h;
-        HIPCHK(c, hipMemcpyAsync(&h, c->d_stats, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        to_public(h, stats);
+        return read_slots(c, c->d_stats, stats);
     }
     return SOC_OK;
 }
@@ -880,7 +897,7 @@ soc_status soc_simulate_frequencies(soc_ctx c, soc_grid g, int32_t K, const soc_
     if ((st = grow(c, &c->d_mpk, c->cap_mpk, std::max<int64_t>(npk, 1)))) return st;
     if ((st = grow(c, &c->d_mS, c->cap_mS, K))) return st;
     if ((st = grow(c, &c->d_margs, c->cap_margs, K))) return st;
-    if ((st = grow(c, &c->d_mcount, c->cap_mcount, K))) return st;
+    if ((st = grow(c, &c->d_mcount, c->cap_mcount, K * kCounterStride))) return st;
     if (njobs > 0) {
         if ((st = grow(c, &c->d_mincl, c->cap_mincl, njobs * g->ncells))) return st;
         if ((st = grow(c, &c->d_msums, c->cap_msums, njobs * scan_elems))) return st;
@@ -909,9 +926,9 @@ soc_status soc_simulate_frequencies(soc_ctx c, soc_grid g, int32_t K, const soc_
         }
         src.S = c->d_mS + k;
         McArgs &A = c->h_margs[k];
-        if ((st = prepare(c, g, &freqs[k], &q, seed, iteration, freq_indices[k], d_absorbed, A, src)))
+        if ((st = prepare(c, g, &freqs[k], &q, seed, iteration, freq_indices[k], d_absorbed, A, src, K)))
             return fail(c, st, "frequency %d: %s", k, c->err.c_str());
-        A.next_id = c->d_mcount + k;
+        A.next_id = c->d_mcount + k * kCounterStride;
     }
     if (njobs > 0) {
         HIPCHK(c, hipMemcpyAsync(c->d_djobs, c->h_djobs.data(), sizeof(DustJob) * (size_t)njobs,
@@ -946,8 +963,7 @@ soc_status soc_simulate_frequencies(soc_ctx c, soc_grid g, int32_t K, const soc_
     }
     HIPCHK(c, hipMemcpyAsync(c->d_margs, c->h_margs.data(), sizeof(McArgs) * (size_t)K, hipMemcpyHostToDevice,
                              c->stream));
-    HIPCHK(c, launch_fill_u64((unsigned long long *)c->d_stats, 0ull, (int64_t)(sizeof(DevStats) / 8), c->stream));
-    HIPCHK(c, launch_fill_u64(c->d_mcount, 0ull, K, c->stream));
+    HIPCHK(c, launch_clear2((unsigned long long *)c->d_stats, kStatWords, c->d_mcount, K * kCounterStride, c->stream));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
         HIPCHK(c, hipEventCreate(&e0));
@@ -971,10 +987,7 @@ soc_status soc_simulate_frequencies(soc_ctx c, soc_grid g, int32_t K, const soc_
         HIPCHK(c, launch_fold_copies(srcs[0].d_ali_self, c->d_priv_self, g->ncells, brick_copies(g), g->nx, g->ny, g->nroot,
                                      c->stream));
     if (stats) {
-        DevStats h;
-        HIPCHK(c, hipMemcpyAsync(&h, c->d_stats, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        to_public(h, stats);
+        return read_slots(c, c->d_stats, stats);
     }
     return SOC_OK;
 }
@@ -1009,17 +1022,13 @@ soc_status soc_simulate_frequency_noalloc(soc_ctx c, soc_grid g, const soc_freq 
             HIPCHK(c, launch_fill_f64(A.priv_self, 0.0, (int64_t)kPrivCopies * g->ncells, c->stream));
         }
     }
-    HIPCHK(c, launch_fill_u64((unsigned long long *)A.st_call, 0ull, (int64_t)(sizeof(DevStats) / 8), c->stream));
-    HIPCHK(c, launch_fill_u64(A.next_id, 0ull, 1, c->stream));
+    HIPCHK(c, launch_clear2((unsigned long long *)A.st_call, kStatWords, A.next_id, 1, c->stream));
     HIPCHK(c, launch_mc(A, (int)(c->num_cus * c->blocks_per_cu), (int)c->block, c->stream));
     if (A.priv) HIPCHK(c, launch_fold_copies(d_absorbed, A.priv, g->ncells, A.brick, g->nx, g->ny, g->nroot, c->stream));
     if (A.priv_self)
         HIPCHK(c, launch_fold_copies(A.ali_self, A.priv_self, g->ncells, A.brick, g->nx, g->ny, g->nroot, c->stream));
     if (stats) {
-        DevStats h;
-        HIPCHK(c, hipMemcpyAsync(&h, A.st_call, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        to_public(h, stats);
+        return read_slots(c, A.st_call, stats);
     }
     return SOC_OK;
 }
@@ -1029,11 +1038,9 @@ soc_status soc_read_stats(soc_ctx c, soc_sim_stats *out, int32_t reset)
     if (!c || !out) return SOC_EINVAL;
     NOT_WHILE_CAPTURING(c);
     HIPCHK(c, hipSetDevice(c->device));
-    DevStats h;
-    HIPCHK(c, hipMemcpyAsync(&h, c->d_stats + 1, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    to_public(h, out);
-    if (reset) HIPCHK(c, launch_fill_u64((unsigned long long *)(c->d_stats + 1), 0ull, (int64_t)(sizeof(DevStats) / 8), c->stream));
+    const soc_status st = read_slots(c, c->d_stats + kStatSlots, out);
+    if (st != SOC_OK) return st;
+    if (reset) HIPCHK(c, launch_fill_u64((unsigned long long *)(c->d_stats + kStatSlots), 0ull, kStatWords, c->stream));
     return SOC_OK;
 }
 
@@ -1075,16 +1082,18 @@ soc_status soc_scatter_map(soc_ctx c, soc_grid g, const soc_freq *f, const soc_s
     P.max_scatter = sp->max_scatter;
     P.direct = sp->direct ? 1 : 0;
     P.image = d_image;
-    if ((st = grow(c, &c->d_peel, c->cap_peel, 8))) return st;
-    HIPCHK(c, launch_fill_f64(c->d_peel, 0.0, 8, c->stream));
+    if ((st = grow(c, &c->d_peel, c->cap_peel, 8 * kStatSlots))) return st;
     P.totals = c->d_peel;
-    HIPCHK(c, launch_fill_u64(c->d_counter, 0ull, 1, c->stream));   // id pool of the refill
+    HIPCHK(c, launch_clear2((unsigned long long *)c->d_peel, 8 * kStatSlots, c->d_counter, 1, c->stream));   // totals, id pool
     const int blocks = (int)(c->num_cus * 8);
+    A.chunk = (int32_t)c->chunk;   // chunks of 64 ids measure 10% slower here (128^3, 10^6 packages)
     HIPCHK(c, launch_peel(A, P, blocks, c->stream));
     if (stats) {
-        double h[6];
-        HIPCHK(c, hipMemcpyAsync(h, c->d_peel, sizeof h, hipMemcpyDeviceToHost, c->stream));
+        double rows[kStatSlots][8], h[6] = {};
+        HIPCHK(c, hipMemcpyAsync(rows, c->d_peel, sizeof rows, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        for (const auto &r : rows)
+            for (int k = 0; k < 6; ++k) h[k] += r[k];
         stats->packages = (uint64_t)h[0];
         stats->cell_steps = (uint64_t)h[1];
         stats->scatterings = (uint64_t)h[2];
@@ -1913,8 +1922,7 @@ soc_status soc_batch_run(soc_batch b, uint32_t iteration, soc_sim_stats *stats)
     if (c->capturing && (stats || c->timing)) return fail(c, SOC_ESTATE, "statistics/timing not allowed during graph capture");
     if (iteration != SOC_ITER_ADVANCE && iteration > 0xFFFFFFu) return fail(c, SOC_EINVAL, "iteration must be < 2^24");
     HIPCHK(c, hipSetDevice(c->device));
-    HIPCHK(c, launch_fill_u64((unsigned long long *)c->d_stats, 0ull, (int64_t)(sizeof(DevStats) / 8), c->stream));
-    HIPCHK(c, launch_fill_i32((int32_t *)b->d_counter, 0, 2, c->stream));
+    HIPCHK(c, launch_clear2((unsigned long long *)c->d_stats, kStatWords, (unsigned long long *)b->d_counter, 1, c->stream));
     HIPCHK(c, launch_advance_iteration(b->d_iteration, iteration == SOC_ITER_ADVANCE ? 1 : 0,
                                        iteration == SOC_ITER_ADVANCE ? 0u : iteration, c->stream));
     BatchArgs a;
@@ -1928,7 +1936,7 @@ soc_status soc_batch_run(soc_batch b, uint32_t iteration, soc_sim_stats *stats)
     a.iteration = b->d_iteration;
     a.step_cap = c->step_cap;
     a.st_call = c->d_stats;
-    a.st_total = c->d_stats + 1;
+    a.st_total = c->d_stats + kStatSlots;
     a.refill_min = (int32_t)c->refill_min;
     a.inner_steps = (int32_t)c->inner_steps;
     a.scatter_min = (int32_t)c->scatter_min;
@@ -1957,10 +1965,7 @@ soc_status soc_batch_run(soc_batch b, uint32_t iteration, soc_sim_stats *stats)
         c->ev_stop.push_back(e1);
     }
     if (stats) {
-        DevStats h;
-        HIPCHK(c, hipMemcpyAsync(&h, c->d_stats, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        to_public(h, stats);
+        return read_slots(c, c->d_stats, stats);
     }
     return SOC_OK;
 }

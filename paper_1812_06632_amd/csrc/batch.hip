@@ -23,31 +23,6 @@
 
 namespace soc {
 
-__device__ inline unsigned long long wsum_u64(unsigned long long v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += (unsigned long long)__shfl_xor((long long)v, o, 64);
-    return v;
-}
-__device__ inline double wsum_f64(double v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ inline void batch_add_stats(DevStats *t, unsigned long long pk, unsigned long long st,
-                                       unsigned long long sc, unsigned long long ru, double em, double ab, double es)
-{
-    atomicAdd(&t->packages, pk);
-    atomicAdd(&t->steps, st);
-    atomicAdd(&t->scatterings, sc);
-    atomicAdd(&t->runaways, ru);
-    unsafeAtomicAdd(&t->emitted, em);
-    unsafeAtomicAdd(&t->absorbed, ab);
-    unsafeAtomicAdd(&t->escaped, es);
-}
-
 // The pair-invariant fields of the view, and the pair's own fields.
 __device__ inline void view_base(BatchView &A, uint32_t iteration, int64_t step_cap)
 {
@@ -285,17 +260,7 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
             }
         }
     }
-    n_pk = wsum_u64(n_pk);
-    n_st = wsum_u64(n_st);
-    n_sc = wsum_u64(n_sc);
-    n_ru = wsum_u64(n_ru);
-    e_em = wsum_f64(e_em);
-    e_ab = wsum_f64(e_ab);
-    e_es = wsum_f64(e_es);
-    if (lane == 0) {
-        batch_add_stats(B.st_call, n_pk, n_st, n_sc, n_ru, e_em, e_ab, e_es);
-        batch_add_stats(B.st_total, n_pk, n_st, n_sc, n_ru, e_em, e_ab, e_es);
-    }
+    flush_stats(B.st_call, B.st_total, n_pk, n_st, n_sc, n_ru, e_em, e_ab, e_es);
 }
 
 hipError_t launch_mc_batch(const BatchArgs &a, int blocks, int threads, int64_t lds_cells, hipStream_t s)

@@ -26,47 +26,6 @@
 
 namespace soc {
 
-__device__ inline unsigned long long wave_sum_u64(unsigned long long v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += (unsigned long long)__shfl_xor((long long)v, o, 64);
-    return v;
-}
-__device__ inline double wave_sum_f64(double v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ inline void add_stats(DevStats *t, unsigned long long pk, unsigned long long st, unsigned long long sc,
-                                 unsigned long long ru, double em, double ab, double es)
-{
-    atomicAdd(&t->packages, pk);
-    atomicAdd(&t->steps, st);
-    atomicAdd(&t->scatterings, sc);
-    atomicAdd(&t->runaways, ru);
-    unsafeAtomicAdd(&t->emitted, em);
-    unsafeAtomicAdd(&t->absorbed, ab);
-    unsafeAtomicAdd(&t->escaped, es);
-}
-
-__device__ inline void flush_stats(const McArgs &A, unsigned long long pk, unsigned long long st,
-                                   unsigned long long sc, unsigned long long ru, double em, double ab, double es)
-{
-    pk = wave_sum_u64(pk);
-    st = wave_sum_u64(st);
-    sc = wave_sum_u64(sc);
-    ru = wave_sum_u64(ru);
-    em = wave_sum_f64(em);
-    ab = wave_sum_f64(ab);
-    es = wave_sum_f64(es);
-    if ((threadIdx.x & 63) == 0) {
-        add_stats(A.st_call, pk, st, sc, ru, em, ab, es);
-        add_stats(A.st_total, pk, st, sc, ru, em, ab, es);
-    }
-}
-
 // Flush of the wave's deposit rings: with diagonal ALI a dust package's
 // deposits in its own emitting cell go to the self-absorption tally, marked
 // by storing the complement of the cell index.
@@ -245,7 +204,7 @@ __device__ __forceinline__ void mc_body(const McArgs &A)
     WaveTally w;
     mc_frequency<Oct, Ali>(A, lds_dep, lds_cell, dst, sdst, w);
     flush_deposits<Ali>(dst, sdst, lds_dep, lds_cell, w.nbuf);
-    flush_stats(A, w.n_pk, w.n_st, w.n_sc, w.n_ru, w.e_em, w.e_ab, w.e_es);
+    flush_stats(A.st_call, A.st_total, w.n_pk, w.n_st, w.n_sc, w.n_ru, w.e_em, w.e_ab, w.e_es);
 }
 
 template <bool Oct>
@@ -285,12 +244,28 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_multi_kernel(MultiArgs M)
     WaveTally w;
     const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
     const int k0 = M.spread ? wave % M.K : 0;
+    const int lane = (int)threadIdx.x & 63;
     for (int j = 0; j < M.K; ++j) {
+        // the next frequency of the rotation that has ids left: the lanes
+        // look at the counters of up to 64 frequencies at once, so that a
+        // wave that comes late passes the drained ones with one load
+        for (;;) {
+            const int i = j + lane;
+            bool left = false;
+            if (i < M.K) {
+                const int q = (k0 + i) % M.K;
+                left = __hip_atomic_load(M.args[q].next_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < M.args[q].n_total;
+            }
+            const unsigned long long m = __ballot(left);
+            j += m ? __ffsll((long long)m) - 1 : 64;
+            if (m || j >= M.K) break;
+        }
+        if (j >= M.K) break;
         const int k = __builtin_amdgcn_readfirstlane((k0 + j) % M.K);
         mc_frequency<Oct, Ali>(args[k], lds_dep, lds_cell, dst, sdst, w);
     }
     flush_deposits<Ali>(dst, sdst, lds_dep, lds_cell, w.nbuf);
-    flush_stats(A0, w.n_pk, w.n_st, w.n_sc, w.n_ru, w.e_em, w.e_ab, w.e_es);
+    flush_stats(A0.st_call, A0.st_total, w.n_pk, w.n_st, w.n_sc, w.n_ru, w.e_em, w.e_ab, w.e_es);
 }
 
 hipError_t launch_mc_multi(const MultiArgs &m, int nlevels, bool ali, int blocks, int threads, hipStream_t s)

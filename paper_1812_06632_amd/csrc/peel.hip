@@ -219,12 +219,15 @@ __global__ __launch_bounds__(256, 3) void peel_kernel(McArgs A, PeelArgs P)
             }
         }
     }
-    // totals: summed over the wave, one set of atomics per wave
+    // totals: summed over the wave, one set of atomics per wave that had packages
+    if (!__any(n_pk != 0ull)) return;
     double v[6] = {(double)n_pk, (double)n_st, (double)n_sc, (double)n_ray, e_em, e_es};
     for (int k = 0; k < 6; ++k)
         for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-    if (lane == 0)
-        for (int k = 0; k < 6; ++k) unsafeAtomicAdd(&P.totals[k], v[k]);
+    if (lane == 0) {
+        double *t = P.totals + 8 * (((blockIdx.x * blockDim.x + threadIdx.x) >> 6) % kStatSlots);
+        for (int k = 0; k < 6; ++k) unsafeAtomicAdd(&t[k], v[k]);
+    }
 }
 
 hipError_t launch_peel(const McArgs &a, const PeelArgs &p, int blocks, hipStream_t s)

@@ -39,6 +39,19 @@ hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t 
 hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s) { return fill(p, v, n, s); }
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) { return fill(p, v, n, s); }
 
+__global__ void clear2_kernel(unsigned long long *a, int64_t na, unsigned long long *b, int64_t nb)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += (int64_t)gridDim.x * blockDim.x)
+        (i < na ? a[i] : b[i - na]) = 0ull;
+}
+
+hipError_t launch_clear2(unsigned long long *a, int64_t na, unsigned long long *b, int64_t nb, hipStream_t s)
+{
+    const int64_t blocks = std::min<int64_t>((na + nb + 255) / 256, 4096);
+    hipLaunchKernelGGL(clear2_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, na, b, nb);
+    return hipGetLastError();
+}
+
 __global__ void copy_f64_kernel(const double *src, double *dst, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)

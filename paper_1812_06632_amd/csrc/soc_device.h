@@ -66,6 +66,51 @@ __device__ inline void flush_rings(const double *lds_dep, const int32_t *lds_cel
     }
 }
 
+// ------------------------------------------------------------------ statistics
+__device__ inline unsigned long long wave_sum_u64(unsigned long long v)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += (unsigned long long)__shfl_xor((long long)v, o, 64);
+    return v;
+}
+__device__ inline double wave_sum_f64(double v)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+__device__ inline void add_stats(DevStats *t, unsigned long long pk, unsigned long long st, unsigned long long sc,
+                                 unsigned long long ru, double em, double ab, double es)
+{
+    atomicAdd(&t->packages, pk);
+    atomicAdd(&t->steps, st);
+    if (sc) atomicAdd(&t->scatterings, sc);
+    if (ru) atomicAdd(&t->runaways, ru);
+    unsafeAtomicAdd(&t->emitted, em);
+    unsafeAtomicAdd(&t->absorbed, ab);
+    unsafeAtomicAdd(&t->escaped, es);
+}
+
+// Add the lanes' totals to the wave's slot of the launch's and of the
+// context's statistics; a wave that had no package has nothing to add.
+__device__ inline void flush_stats(DevStats *call, DevStats *total, unsigned long long pk, unsigned long long st,
+                                   unsigned long long sc, unsigned long long ru, double em, double ab, double es)
+{
+    if (!__any(pk != 0ull)) return;
+    pk = wave_sum_u64(pk);
+    st = wave_sum_u64(st);
+    sc = wave_sum_u64(sc);
+    ru = wave_sum_u64(ru);
+    em = wave_sum_f64(em);
+    ab = wave_sum_f64(ab);
+    es = wave_sum_f64(es);
+    if ((threadIdx.x & 63) == 0) {
+        const uint32_t slot = ((blockIdx.x * blockDim.x + threadIdx.x) >> 6) % kStatSlots;
+        add_stats(call + slot, pk, st, sc, ru, em, ab, es);
+        add_stats(total + slot, pk, st, sc, ru, em, ab, es);
+    }
+}
 
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 (Salmon, Moraes, Dror & Shaw, SC'11): ten rounds of two

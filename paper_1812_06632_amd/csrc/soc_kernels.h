@@ -41,10 +41,19 @@ struct PsArg {
     double W;         // energy per package
 };
 
-struct DevStats {
+// Totals of a launch or a context: kStatSlots partial sums, each in a
+// 64-byte line of its own (the waves of a launch end together, and the memory
+// side takes adds to one line one after the other: 3072 waves adding their
+// 14 values to one line cost a small launch more than its packages), added
+// up by the host when they are read.
+constexpr int kStatSlots = 64;
+struct alignas(64) DevStats {
     unsigned long long packages, steps, scatterings, runaways;
     double emitted, absorbed, escaped;
 };
+constexpr int64_t kStatWords = kStatSlots * (int64_t)(sizeof(DevStats) / 8);
+// 64-bit words from one package-id counter to the next (a line each)
+constexpr int64_t kCounterStride = 16;
 
 // Everything one Monte Carlo launch needs, passed by value.
 struct McArgs {
@@ -82,14 +91,14 @@ struct McArgs {
     double *priv_self;           // NULL, or kPrivCopies private copies of ali_self
     // persistent scheduling
     unsigned long long *next_id;
-    DevStats *st_call, *st_total;
+    DevStats *st_call, *st_total;   // kStatSlots each
     int32_t refill_min, inner_steps, chunk, scatter_min;
 };
 
 // Scattered-light image (peel-off).  The observer is along +/- axis; the
 // image has npy rows of npx pixels of edge psz root units; scale is
-// 1 / (A_pix w_nu).  totals: packages, steps, scatterings, ray-march steps,
-// emitted and escaped energy (device doubles, +=).
+// 1 / (A_pix w_nu).  totals: kStatSlots rows of 8 doubles, each packages,
+// steps, scatterings, ray-march steps, emitted and escaped energy (+=).
 struct PeelArgs {
     int32_t axis, npx, npy, forced, max_scatter, direct;
     float ox, oy, oz;
@@ -177,6 +186,8 @@ hipError_t launch_peel(const McArgs &a, const PeelArgs &p, int blocks, hipStream
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s);
 hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
+// Zero na words at a and nb words at b in one launch.
+hipError_t launch_clear2(unsigned long long *a, int64_t na, unsigned long long *b, int64_t nb, hipStream_t s);
 // absorbed[c] += sum_x priv[x n + c] over the kPrivCopies private copies, which are left zero.
 // Add the private copies into absorbed and clear them; brick: their first
 // nroot entries are the root cells of an nx x ny x nz root grid (even

@@ -1,0 +1,50 @@
+"""Launches with few packages: chunks of 64 ids, statistics in slots, and a
+rotation over more frequencies than a wave looks at once, some of them
+without packages."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_bg", [1, 63, 64, 65, 5000])
+def test_every_package_is_counted_once(n_bg):
+    from paper_1812_06632_amd import soc, workloads as W
+
+    P = W.sphere_problem(n=8, n_packages=n_bg)
+    ctx = soc.Context(0)
+    g = soc.grid_from_workload(ctx, P.grid)
+    f = (float(P.nu[0]), float(P.w[0]), float(P.sigma_abs[0]), float(P.sigma_sca[0]), float(P.g[0]))
+    A = torch.zeros(P.grid.ncells, dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        A.zero_()
+        st = soc.simulate_frequency(ctx, g, f, A, I_bg=float(P.I_bg[0]), n_bg=n_bg, seed=3, stats=True)
+        assert st["packages"] == n_bg
+        assert abs(float(A.sum()) + st["e_escaped"] - st["e_emitted"]) <= 1e-9 * st["e_emitted"]
+    total = ctx.read_stats(reset=True)
+    assert total["packages"] == 2 * n_bg and ctx.read_stats()["packages"] == 0
+
+
+@pytest.mark.parametrize("spread", [0, 1])
+def test_rotation_over_many_frequencies(spread):
+    from paper_1812_06632_amd import soc, workloads as W
+
+    K = 130
+    P = W.lognormal_problem(n=8, K=K)
+    ctx = soc.Context(0)
+    ctx.set_option("multi_spread", spread)
+    g = soc.grid_from_workload(ctx, P.grid)
+    freqs = [(float(P.nu[k]), float(P.w[k]), float(P.sigma_abs[k]), float(P.sigma_sca[k]), float(P.g[k])) for k in range(K)]
+    counts = [0 if k < 66 or k % 7 == 0 else 40 + k for k in range(K)]
+    src = [dict(I_bg=float(P.I_bg[k]), n_bg=counts[k]) for k in range(K)]
+    A = torch.zeros(P.grid.ncells, dtype=torch.float64, device="cuda")
+    B = torch.zeros_like(A)
+    st = soc.simulate_frequencies(ctx, g, freqs, A, src, range(K), seed=5, iteration=1, stats=True)
+    steps = 0
+    for k in range(K):
+        one = soc.simulate_frequency(ctx, g, freqs[k], B, seed=5, iteration=1, freq_index=k, stats=True, **src[k])
+        steps += one["cell_steps"]
+    assert st["packages"] == sum(counts) and st["cell_steps"] == steps
+    # the same FP64 deposits in another order
+    np.testing.assert_allclose(A.cpu().numpy(), B.cpu().numpy(), rtol=1e-11)
