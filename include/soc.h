@@ -438,18 +438,19 @@ typedef struct {
 
 typedef struct soc_batch_s *soc_batch;
 /* Copies the pair table and the tile queue (tiles of at most tile_packages
- * ids, ordered by decreasing estimated cost) to the device.  Pairs whose
- * grid has at most SOC_OPT_BATCH_LDS_CELLS cells (the option's value now)
- * are not tiled: each is one work item of a workgroup that tallies the
- * grid in LDS, taken before the tiles (same random numbers and results up
- * to FP64 summation order).  A batch with such pairs launches 512-lane
+ * ids, fewer in a batch too small to give every wave several tiles; ordered
+ * by decreasing estimated cost) to the device.  Pairs whose grid has at
+ * most SOC_OPT_BATCH_LDS_CELLS cells (the option's value now) are not
+ * tiled: each is one work item, or a few in a batch of few such pairs, of a
+ * workgroup that tallies the grid in LDS, taken before the tiles (same
+ * random numbers and results up to FP64 summation order).  A batch with such pairs launches 512-lane
  * workgroups, one or two per compute unit as their LDS allows
  * (SOC_OPT_BLOCK and SOC_OPT_BLOCKS_PER_CU shape the other batches).
  * With SOC_OPT_XCD_COPIES 1 (now), an array that only tiled pairs of one
  * grid with even dimensions add into is tallied in a batch-owned scratch
  * copy in 2 x 2 x 2 brick order (one FP64 per cell of every such array),
  * which each soc_batch_run adds into the array after its launch and leaves
- * zero.  Synchronises.  soc_batch_info counts the LDS pairs among the
+ * zero.  Synchronises.  soc_batch_info counts the LDS items among the
  * tiles. */
 soc_status soc_batch_create(soc_ctx ctx, int32_t n_grids, const soc_grid *grids, int32_t n_pairs,
                             const soc_batch_pair *pairs, uint64_t seed, uint64_t tile_packages, soc_batch *out);

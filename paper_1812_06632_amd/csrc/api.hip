@@ -102,8 +102,8 @@ struct soc_batch_s {
     PsArg *d_ps = nullptr;
     unsigned int *d_counter = nullptr;      // [0] next tile, [1] next LDS pair
     uint32_t *d_iteration = nullptr;
-    int32_t *d_lds_pairs = nullptr;         // pairs of small grids, largest cost first
-    int32_t n_lds_pairs = 0;
+    TileDev *d_lds_items = nullptr;         // pairs of small grids or parts of them, largest cost first
+    int32_t n_lds_items = 0;
     int64_t lds_cells = 0;                  // the largest grid among them
     double *d_brick = nullptr;              // brick-ordered tallies of the tiled arrays (zero between runs)
     BrickFold *d_folds = nullptr;           // each tally and its array
@@ -1721,6 +1721,23 @@ soc_status soc_surrogate_apply_absorbed(soc_ctx c, soc_grid g, int32_t S, const 
     return SOC_OK;
 }
 
+// Launch shape of a batch under the context's present options.
+namespace {
+struct BatchLaunch {
+    int blocks, threads;
+};
+BatchLaunch batch_launch(soc_ctx c, bool lds, int64_t lds_cells)
+{
+    if (!lds) return BatchLaunch{(int)(c->num_cus * c->blocks_per_cu), (int)c->block};
+    // a workgroup holds a small grid's tally: 512-lane workgroups, as many
+    // per compute unit as their LDS allows (at most two)
+    const int64_t ring = (int64_t)kRingStride * kMcMaxBlock * (int64_t)(sizeof(double) + sizeof(int32_t));
+    const int64_t need = std::max<int64_t>(ring, lds_cells * (int64_t)sizeof(double)) + 256;
+    const int64_t per_cu = std::min<int64_t>(2, std::max<int64_t>(1, c->lds_per_cu / need));
+    return BatchLaunch{(int)(c->num_cus * per_cu), kMcMaxBlock};
+}
+}  // namespace
+
 soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, int32_t n_pairs,
                             const soc_batch_pair *pairs, uint64_t seed, uint64_t tile_packages, soc_batch *out)
 {
@@ -1737,9 +1754,9 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
     std::vector<PsArg> hps;
     std::vector<int64_t> ps_off(n_pairs, 0);
     struct TileCost { double cost; TileDev t; };
-    std::vector<TileCost> tiles;
-    struct LdsPair { double cost; int32_t pair; };
-    std::vector<LdsPair> lds;
+    std::vector<TileCost> tiles, lds;
+    uint64_t lds_total = 0;
+    int64_t lds_cells = 0;
     uint64_t total = 0;
     for (int32_t i = 0; i < n_pairs; ++i) {
         const soc_batch_pair &q = pairs[i];
@@ -1787,24 +1804,39 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
         P.key0 = (uint32_t)seed;
         P.key1 = (uint32_t)(seed >> 32) ^ (uint32_t)q.grid;
         P.freq_index = q.freq_index;
-        // tiles, costed by packages x (optical size + grid extent); a pair
-        // of a small grid is one workgroup's whole (LDS tally)
-        const double extent = (double)(g->nx + g->ny + g->nz);
-        if (g->ncells <= c->batch_lds_cells) {
-            if (P.n_total > 0) lds.push_back({(double)P.n_total * extent, i});
-            total += P.n_total;
-            continue;
+        total += P.n_total;
+        if (g->ncells <= c->batch_lds_cells && P.n_total > 0) {
+            lds_total += P.n_total;
+            lds_cells = std::max<int64_t>(lds_cells, g->ncells);
         }
-        for (uint64_t b = 0; b < P.n_total; b += tile_packages) {
+    }
+    // Cut the pairs into work items of ids: tiles that a wave takes, or, for
+    // a pair of a small grid, items that a workgroup tallies in LDS.  At
+    // least eight items per wave or workgroup of the launch, so that the last
+    // ones end together, in items of 256 and 4096 packages or more: a wave
+    // spends about a hundredth of a tile of 256 on taking it and on its last
+    // flush, and a workgroup 20 us of an item of 4096 (about 0.5 ms) on
+    // clearing and adding out its LDS tally.  24 clouds of 16^3 to 72^3
+    // cells, 8 frequencies, 7e6 packages: 7.8 ms (four items: 8.1 ms), 50 ms
+    // with whole pairs and tiles of 16384.
+    const BatchLaunch shape = batch_launch(c, lds_total > 0, lds_cells);
+    const uint64_t tile = std::min<uint64_t>(
+        tile_packages, std::max<uint64_t>(256, (total - lds_total) / (8ull * shape.blocks * (shape.threads / 64))));
+    const uint64_t item = std::max<uint64_t>(4096, lds_total / (8ull * shape.blocks));
+    for (int32_t i = 0; i < n_pairs; ++i) {
+        const soc_grid g = grids[pairs[i].grid];
+        const bool small = g->ncells <= c->batch_lds_cells;
+        const double extent = (double)(g->nx + g->ny + g->nz);   // an id's cost: cells it may cross
+        const uint64_t n = hp[i].n_total, size = small ? item : tile, parts = (n + size - 1) / size;
+        for (uint64_t k = 0; k < parts; ++k) {
             TileCost tc;
             tc.t.pair = i;
-            tc.t.begin = (uint32_t)b;
-            tc.t.end = (uint32_t)std::min<uint64_t>(P.n_total, b + tile_packages);
+            tc.t.begin = (uint32_t)(n * k / parts);
+            tc.t.end = (uint32_t)(n * (k + 1) / parts);
             tc.t.pad = 0;
             tc.cost = (double)(tc.t.end - tc.t.begin) * extent;
-            tiles.push_back(tc);
+            (small ? lds : tiles).push_back(tc);
         }
-        total += P.n_total;
     }
     // brick-ordered tallies (private copies on): one per array that only
     // tiled pairs of one grid with even dimensions add into
@@ -1837,13 +1869,9 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
         max_fold_cells = std::max<int64_t>(max_fold_cells, g->ncells);
     }
     std::stable_sort(tiles.begin(), tiles.end(), [](const TileCost &a, const TileCost &b) { return a.cost > b.cost; });
-    std::stable_sort(lds.begin(), lds.end(), [](const LdsPair &a, const LdsPair &b) { return a.cost > b.cost; });
-    std::vector<int32_t> hl(lds.size());
-    int64_t lds_cells = 0;
-    for (size_t i = 0; i < lds.size(); ++i) {
-        hl[i] = lds[i].pair;
-        lds_cells = std::max<int64_t>(lds_cells, hp[lds[i].pair].ncells);
-    }
+    std::stable_sort(lds.begin(), lds.end(), [](const TileCost &a, const TileCost &b) { return a.cost > b.cost; });
+    std::vector<TileDev> hl(lds.size());
+    for (size_t i = 0; i < lds.size(); ++i) hl[i] = lds[i].t;
     HIPCHK(c, hipSetDevice(c->device));
     soc_batch b = new (std::nothrow) soc_batch_s;
     if (!b) return fail(c, SOC_ENOMEM, "host allocation");
@@ -1851,7 +1879,7 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
     b->device = c->device;
     b->n_tiles = (int32_t)tiles.size();
     b->n_packages = total;
-    b->n_lds_pairs = (int32_t)hl.size();
+    b->n_lds_items = (int32_t)hl.size();
     b->lds_cells = lds_cells;
     b->n_folds = (int32_t)folds.size();
     b->max_fold_cells = max_fold_cells;
@@ -1864,7 +1892,7 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
         hipMalloc((void **)&b->d_ps, sizeof(PsArg) * std::max<size_t>(1, hps.size())) != hipSuccess ||
         hipMalloc((void **)&b->d_counter, 2 * sizeof(unsigned int)) != hipSuccess ||
         hipMalloc((void **)&b->d_iteration, sizeof(uint32_t)) != hipSuccess ||
-        hipMalloc((void **)&b->d_lds_pairs, sizeof(int32_t) * std::max<size_t>(1, hl.size())) != hipSuccess ||
+        hipMalloc((void **)&b->d_lds_items, sizeof(TileDev) * std::max<size_t>(1, hl.size())) != hipSuccess ||
         hipMalloc((void **)&b->d_folds, sizeof(BrickFold) * std::max<size_t>(1, folds.size())) != hipSuccess ||
         (brick_cells > 0 && hipMalloc((void **)&b->d_brick, sizeof(double) * (size_t)brick_cells) != hipSuccess))
         return cleanup(fail(c, SOC_ENOMEM, "batch tables"));
@@ -1882,7 +1910,7 @@ soc_status soc_batch_create(soc_ctx c, int32_t n_grids, const soc_grid *grids, i
     if (hipMemcpy(b->d_pairs, hp.data(), sizeof(PairDev) * n_pairs, hipMemcpyHostToDevice) != hipSuccess ||
         (ht.size() && hipMemcpy(b->d_tiles, ht.data(), sizeof(TileDev) * ht.size(), hipMemcpyHostToDevice) != hipSuccess) ||
         (hps.size() && hipMemcpy(b->d_ps, hps.data(), sizeof(PsArg) * hps.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        (hl.size() && hipMemcpy(b->d_lds_pairs, hl.data(), sizeof(int32_t) * hl.size(), hipMemcpyHostToDevice) != hipSuccess) ||
+        (hl.size() && hipMemcpy(b->d_lds_items, hl.data(), sizeof(TileDev) * hl.size(), hipMemcpyHostToDevice) != hipSuccess) ||
         (folds.size() && hipMemcpy(b->d_folds, folds.data(), sizeof(BrickFold) * folds.size(), hipMemcpyHostToDevice) != hipSuccess))
         return cleanup(fail(c, SOC_EHIP, "batch upload"));
     if (launch_advance_iteration(b->d_iteration, 0, 0u, c->stream) != hipSuccess ||
@@ -1901,7 +1929,7 @@ void soc_batch_destroy(soc_batch b)
     (void)hipFree(b->d_ps);
     (void)hipFree(b->d_counter);
     (void)hipFree(b->d_iteration);
-    (void)hipFree(b->d_lds_pairs);
+    (void)hipFree(b->d_lds_items);
     (void)hipFree(b->d_folds);
     (void)hipFree(b->d_brick);
     delete b;
@@ -1910,7 +1938,7 @@ void soc_batch_destroy(soc_batch b)
 soc_status soc_batch_info(soc_batch b, int32_t *n_tiles, uint64_t *n_packages)
 {
     if (!b) return SOC_EINVAL;
-    if (n_tiles) *n_tiles = b->n_tiles + b->n_lds_pairs;
+    if (n_tiles) *n_tiles = b->n_tiles + b->n_lds_items;
     if (n_packages) *n_packages = b->n_packages;
     return SOC_OK;
 }
@@ -1930,8 +1958,8 @@ soc_status soc_batch_run(soc_batch b, uint32_t iteration, soc_sim_stats *stats)
     a.tiles = b->d_tiles;
     a.n_tiles = b->n_tiles;
     a.next_tile = b->d_counter;
-    a.lds_pairs = b->d_lds_pairs;
-    a.n_lds_pairs = b->n_lds_pairs;
+    a.lds_items = b->d_lds_items;
+    a.n_lds_items = b->n_lds_items;
     a.next_lds = b->d_counter + 1;
     a.iteration = b->d_iteration;
     a.step_cap = c->step_cap;
@@ -1940,24 +1968,14 @@ soc_status soc_batch_run(soc_batch b, uint32_t iteration, soc_sim_stats *stats)
     a.refill_min = (int32_t)c->refill_min;
     a.inner_steps = (int32_t)c->inner_steps;
     a.scatter_min = (int32_t)c->scatter_min;
-    a.chunk = (int32_t)c->chunk;
-    int blocks = (int)(c->num_cus * c->blocks_per_cu), threads = (int)c->block;
-    if (b->n_lds_pairs > 0) {
-        // a workgroup holds a small grid's tally: 512-lane workgroups, as many
-        // per compute unit as their LDS allows (at most two)
-        threads = kMcMaxBlock;
-        const int64_t ring = (int64_t)kRingStride * threads * (int64_t)(sizeof(double) + sizeof(int32_t));
-        const int64_t need = std::max<int64_t>(ring, b->lds_cells * (int64_t)sizeof(double)) + 256;
-        const int64_t per_cu = std::min<int64_t>(2, std::max<int64_t>(1, c->lds_per_cu / need));
-        blocks = (int)(c->num_cus * per_cu);
-    }
+    const BatchLaunch shape = batch_launch(c, b->n_lds_items > 0, b->lds_cells);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
         HIPCHK(c, hipEventCreate(&e0));
         HIPCHK(c, hipEventCreate(&e1));
         HIPCHK(c, hipEventRecord(e0, c->stream));
     }
-    HIPCHK(c, launch_mc_batch(a, blocks, threads, b->lds_cells, c->stream));
+    HIPCHK(c, launch_mc_batch(a, shape.blocks, shape.threads, b->lds_cells, c->stream));
     HIPCHK(c, launch_batch_fold(b->d_folds, b->n_folds, b->max_fold_cells, c->stream));
     if (c->timing) {
         HIPCHK(c, hipEventRecord(e1, c->stream));

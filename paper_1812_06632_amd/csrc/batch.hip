@@ -11,12 +11,13 @@
 // batch_fold_kernel.  Pair parameters are read as wave-uniform (scalar)
 // data at each tile switch.
 //
-// Pairs of small grids come first and differently: a workgroup takes a
-// whole pair, keeps that grid's absorbed array in LDS, and its waves add
-// every deposit there (LDS atomics: ~25x the rate of the memory-side
-// global atomics that bound the rest); when the pair is done the
-// workgroup adds the LDS array to the model's array, one coalesced add
-// per cell.  Then the same LDS serves as the deposit ring of the tiles.
+// Pairs of small grids come first and differently: a workgroup takes an
+// item, a whole pair or an even part of its ids, keeps that grid's absorbed
+// array in LDS, and its waves add every deposit there (LDS atomics: ~25x
+// the rate of the memory-side global atomics that bound the rest); when the
+// item is done the workgroup adds the LDS array to the model's array, one
+// coalesced add per cell.  Then the same LDS serves as the deposit ring of
+// the tiles.
 #include <algorithm>
 
 #include "soc_device.h"
@@ -55,11 +56,14 @@ __device__ inline void view_pair(BatchView &A, const PairDev &P)
     A.key0 = P.key0; A.key1 = P.key1; A.freq_index = P.freq_index;
 }
 
+// Ids a wave of the LDS phase takes at a time (the counter is in LDS).
+constexpr int kLdsChunk = 64;
+
 __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
 {
     extern __shared__ double lds_dep[];   // LDS phase: a grid's tally; tiles: [blockDim.x][kRingStride] deposits, then cells
     int32_t *lds_cell = (int32_t *)(lds_dep + kRingStride * blockDim.x);
-    __shared__ int32_t sh_pair;                // pair of the LDS phase, workgroup-uniform
+    __shared__ int32_t sh_item;                // item of the LDS phase, workgroup-uniform
     __shared__ unsigned long long sh_next;     // its next unassigned package id
     const int tid = threadIdx.x;
     const int bd = blockDim.x;
@@ -69,20 +73,22 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
     unsigned long long n_pk = 0, n_st = 0, n_sc = 0, n_ru = 0;
     double e_em = 0.0, e_ab = 0.0, e_es = 0.0;
 
-    // ---- small grids: one whole pair per workgroup, tallied in LDS
-    if (B.n_lds_pairs > 0) {
+    // ---- small grids: one item per workgroup, tallied in LDS
+    if (B.n_lds_items > 0) {
         BatchView A;
         view_base(A, iteration, B.step_cap);
         for (;;) {
-            __syncthreads();   // the previous pair's LDS array has been added out
+            __syncthreads();   // the previous item's LDS array has been added out
             if (tid == 0) {
-                sh_pair = (int32_t)atomicAdd(B.next_lds, 1u);
-                sh_next = 0ull;
+                sh_item = (int32_t)atomicAdd(B.next_lds, 1u);
+                if (sh_item < B.n_lds_items) sh_next = B.lds_items[sh_item].begin;
             }
             __syncthreads();
-            const int32_t q = sh_pair;
-            if (q >= B.n_lds_pairs) break;
-            const PairDev &P = B.pairs[B.lds_pairs[q]];
+            const int32_t q = __builtin_amdgcn_readfirstlane(sh_item);
+            if (q >= B.n_lds_items) break;
+            const TileDev item = B.lds_items[q];
+            const unsigned long long id_end = __builtin_amdgcn_readfirstlane(item.end);
+            const PairDev &P = B.pairs[__builtin_amdgcn_readfirstlane(item.pair)];
             view_pair(A, P);
             const int32_t nc = (int32_t)P.ncells;
             for (int32_t c = tid; c < nc; c += bd) lds_dep[c] = 0.0;
@@ -102,13 +108,13 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
                     if (avail < (unsigned long long)nidle) {
                         const int leader = __ffsll((long long)idle) - 1;
                         unsigned long long g0 = 0;
-                        if (lane == leader) g0 = atomicAdd(&sh_next, (unsigned long long)B.chunk);
+                        if (lane == leader) g0 = atomicAdd(&sh_next, (unsigned long long)kLdsChunk);
                         grant = (unsigned long long)__shfl((long long)g0, leader, 64);
                     }
                     if (!active) {
                         const unsigned long long r = (unsigned long long)__popcll(idle & below);
                         const unsigned long long id = r < avail ? pool_next + r : grant + (r - avail);
-                        if (id < A.n_total) {
+                        if (id < id_end) {
                             uint32_t cls, pid;
                             double W0;
                             const bool ok = emit<float, false>(A, id, p, rng, cls, pid, W0);
@@ -119,11 +125,11 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
                     }
                     if (avail < (unsigned long long)nidle) {
                         pool_next = grant + ((unsigned long long)nidle - avail);
-                        pool_end = grant + (unsigned long long)B.chunk;
+                        pool_end = grant + (unsigned long long)kLdsChunk;
                     } else {
                         pool_next += (unsigned long long)nidle;
                     }
-                    if (pool_next >= A.n_total) exhausted = true;
+                    if (pool_next >= id_end) exhausted = true;
                 }
                 if (!__any(active)) {
                     if (exhausted) break;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
                     }
                 }
             }
-            __syncthreads();   // every wave has finished the pair
+            __syncthreads();   // every wave has finished the item
             for (int32_t c = tid; c < nc; c += bd) {
                 const double v = lds_dep[c];
                 if (v != 0.0) unsafeAtomicAdd(&P.absorbed[c], v);
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
 hipError_t launch_mc_batch(const BatchArgs &a, int blocks, int threads, int64_t lds_cells, hipStream_t s)
 {
     const size_t ring = (size_t)kRingStride * threads * (sizeof(double) + sizeof(int32_t));
-    const size_t tally = a.n_lds_pairs > 0 ? (size_t)lds_cells * sizeof(double) : 0;
+    const size_t tally = a.n_lds_items > 0 ? (size_t)lds_cells * sizeof(double) : 0;
     hipLaunchKernelGGL(mc_batch_kernel, dim3(blocks), dim3(threads), ring > tally ? ring : tally, s, a);
     return hipGetLastError();
 }

@@ -359,13 +359,13 @@ struct BatchArgs {
     const TileDev *tiles;
     int32_t n_tiles;
     unsigned int *next_tile;
-    const int32_t *lds_pairs;    // pairs a workgroup takes whole, tallied in LDS (small grids)
-    int32_t n_lds_pairs;
+    const TileDev *lds_items;    // pairs of small grids, or parts of them, that a workgroup tallies in LDS
+    int32_t n_lds_items;
     unsigned int *next_lds;
     const uint32_t *iteration;   // device word, read at launch
     int64_t step_cap;
     DevStats *st_call, *st_total;
-    int32_t refill_min, inner_steps, scatter_min, chunk;
+    int32_t refill_min, inner_steps, scatter_min;
 };
 
 // The lean per-pair view the emission and step code read in the batched
@@ -391,7 +391,7 @@ struct BatchView {
     int64_t step_cap;
 };
 
-// lds_cells: the largest grid of a.lds_pairs (the LDS tally's size)
+// lds_cells: the largest grid of a.lds_items (the LDS tally's size)
 hipError_t launch_mc_batch(const BatchArgs &a, int blocks, int threads, int64_t lds_cells, hipStream_t s);
 // A brick-ordered tally of the batch and the array it is added to.
 struct BrickFold {

@@ -48,3 +48,32 @@ def test_rotation_over_many_frequencies(spread):
     assert st["packages"] == sum(counts) and st["cell_steps"] == steps
     # the same FP64 deposits in another order
     np.testing.assert_allclose(A.cpu().numpy(), B.cpu().numpy(), rtol=1e-11)
+
+
+@pytest.mark.parametrize("n_bg", [1, 4095, 4097, 20000])
+@pytest.mark.parametrize("lds", [0, 13824])
+def test_batch_items_cover_every_id(n_bg, lds):
+    """Pairs cut into several LDS items or small tiles add up to the single
+    calls."""
+    from paper_1812_06632_amd import soc, workloads as W
+
+    ctx = soc.Context(0)
+    ctx.set_option("batch_lds_cells", lds)
+    grids, (nu, w, sabs, ssca, hg, I), _ = W.batch_clouds(n_models=3, K=2, n_min=8, n_max=16)
+    G = [soc.grid_from_workload(ctx, g) for g in grids]
+    f = [(float(nu[k]), float(w[k]), float(sabs[k]), float(ssca[k]), float(hg[k])) for k in range(2)]
+    A = [torch.zeros(g.ncells, dtype=torch.float64, device="cuda") for g in G]
+    pairs = [dict(grid=m, freq=f[k], freq_index=k, absorbed=A[m], I_bg=float(I[k]), n_bg=n_bg) for m in range(3) for k in range(2)]
+    b = soc.Batch(ctx, G, pairs, seed=11)
+    assert b.info()[1] == 6 * n_bg
+    st = b.run(iteration=2, stats=True)
+    assert st["packages"] == 6 * n_bg
+    steps = 0
+    for m in range(3):
+        B = torch.zeros_like(A[m])
+        for k in range(2):
+            steps += soc.simulate_frequency(ctx, G[m], f[k], B, I_bg=float(I[k]), n_bg=n_bg, seed=11 ^ (m << 32), iteration=2,
+                                            freq_index=k, stats=True)["cell_steps"]
+        # the same FP64 deposits in another order
+        np.testing.assert_allclose(A[m].cpu().numpy(), B.cpu().numpy(), rtol=1e-11)
+    assert st["cell_steps"] == steps
