@@ -60,6 +60,8 @@ struct soc_ctx_s {
     int64_t cap_priv_self = 0;
     double *d_peel = nullptr;                 // totals of a scattered-light run
     int64_t cap_peel = 0;
+    double *d_shg = nullptr;                  // emissions of the size parts of a grain solve
+    int64_t cap_shg = 0;
     double *d_L = nullptr, *d_incl = nullptr, *d_scan = nullptr;
     int64_t cap_L = 0, cap_incl = 0, cap_scan = 0;
     double *d_a = nullptr, *d_S = nullptr;   // selection weights / capped counts; sum of |L| (capped mode)
@@ -575,6 +577,7 @@ void soc_ctx_destroy(soc_ctx c)
     (void)hipFree(c->d_priv);
     (void)hipFree(c->d_priv_self);
     (void)hipFree(c->d_peel);
+    (void)hipFree(c->d_shg);
     (void)hipFree(c->d_L);
     (void)hipFree(c->d_incl);
     (void)hipFree(c->d_a);
@@ -1137,28 +1140,46 @@ soc_status soc_shg_model_create(soc_ctx c, int32_t K, const double *nu, const do
     m->device = c->device;
     m->S = S; m->K = K; m->N = N;
     const int64_t sk = (int64_t)S * K, sn = (int64_t)S * N;
-    // layout: nu hnu inv_hnu w | abundance | sigma | U | T | share | emit | icool | idu | ks (bytes) | band (int32)
-    int64_t ks_off = 4 * (int64_t)K + S + sk + 2 * sn + sk + sn * K + sn + sn;
-    ks_off += ks_off & 1;   // 16-byte aligned
-    const int64_t total = ks_off + ((int64_t)S * shg_ks_stride(N) + 4 * (int64_t)S + 7) / 8;
+    const int64_t n_emit = (int64_t)S * shg_tiles(K) * shg_steps(N) * 128, n_first = (int64_t)S * shg_tiles(N) * shg_steps(K) * 128;
+    // layout (16-byte aligned parts): nu hnu inv_hnu w abundance sigma U T | rate icool | first emit | stream |
+    // first_block | count
+    const auto even = [](int64_t n) { return (n + 1) & ~int64_t(1); };
+    std::vector<double> h;
+    ShgStream st;
+    const double hP = 6.62607015e-27;
+    try {
+        h.resize((size_t)even(4 * (int64_t)K + S + sk + 2 * sn));
+        for (int k = 0; k < K; ++k) {
+            h[k] = nu[k];
+            h[K + k] = hP * nu[k];
+            h[2 * K + k] = 1.0 / (hP * nu[k]);
+            h[3 * K + k] = w[k];
+        }
+        std::memcpy(&h[4 * K], abundance, sizeof(double) * S);
+        std::memcpy(&h[4 * K + S], sigma, sizeof(double) * sk);
+        std::memcpy(&h[4 * K + S + sk], U, sizeof(double) * sn);
+        std::memcpy(&h[4 * K + S + sk + sn], T, sizeof(double) * sn);
+        shg_build_stream(S, K, N, &h[K], U, st);
+    } catch (const std::bad_alloc &) {
+        delete m;
+        return fail(c, SOC_ENOMEM, "out of host memory");
+    }
+    const int64_t o_rate = (int64_t)h.size(), o_icool = o_rate + (int64_t)S * 8 * shg_steps(K), o_first = o_icool + even(sn);
+    const int64_t o_emit = o_first + n_first, o_stream = o_emit + n_emit;
+    const int64_t o_block = o_stream + (int64_t)st.words.size() / 2, o_count = o_block + (S + 1) / 2;
+    const int64_t total = o_count + (sn + 3) / 4;
     if (hipMalloc((void **)&m->d_buf, sizeof(double) * (size_t)total) != hipSuccess) {
         delete m;
         return fail(c, SOC_ENOMEM, "device allocation of the grain model failed");
     }
-    std::vector<double> h(4 * (size_t)K + S + sk + 2 * sn);
-    const double hP = 6.62607015e-27;
-    for (int k = 0; k < K; ++k) {
-        h[k] = nu[k];
-        h[K + k] = hP * nu[k];
-        h[2 * K + k] = 1.0 / (hP * nu[k]);
-        h[3 * K + k] = w[k];
-    }
-    std::memcpy(&h[4 * K], abundance, sizeof(double) * S);
-    std::memcpy(&h[4 * K + S], sigma, sizeof(double) * sk);
-    std::memcpy(&h[4 * K + S + sk], U, sizeof(double) * sn);
-    std::memcpy(&h[4 * K + S + sk + sn], T, sizeof(double) * sn);
     double *d = m->d_buf;
-    hipError_t e = hipMemcpyAsync(d, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, c->stream);
+    const auto up = [&](int64_t at, const void *src, size_t bytes) {
+        return hipMemcpyAsync(d + at, src, bytes, hipMemcpyHostToDevice, c->stream);
+    };
+    hipError_t e = up(0, h.data(), sizeof(double) * h.size());
+    if (e == hipSuccess) e = up(o_stream, st.words.data(), sizeof(uint32_t) * st.words.size());
+    if (e == hipSuccess) e = up(o_block, st.first_block.data(), sizeof(int32_t) * st.first_block.size());
+    if (e == hipSuccess) e = up(o_count, st.count.data(), sizeof(uint16_t) * st.count.size());
     soc::ShgModelDev &v = m->dev;
     v.S = S; v.K = K; v.N = N;
     v.nu = d; v.hnu = d + K; v.inv_hnu = d + 2 * K;
@@ -1167,12 +1188,13 @@ soc_status soc_shg_model_create(soc_ctx c, int32_t K, const double *nu, const do
     v.sigma = d + 4 * K + S;
     v.U = d + 4 * K + S + sk;
     v.T = d + 4 * K + S + sk + sn;
-    v.share = d + 4 * K + S + sk + 2 * sn;
-    v.emit = v.share + sk;
-    v.icool = v.emit + sn * K;
-    v.idu = v.icool + sn;
-    v.ks = (uint8_t *)(d + ks_off);
-    v.band = (int32_t *)(v.ks + (int64_t)S * shg_ks_stride(N));
+    v.rate = d + o_rate;
+    v.icool = d + o_icool;
+    v.first = d + o_first;
+    v.emit = d + o_emit;
+    v.stream = (const uint32_t *)(d + o_stream);
+    v.first_block = (const int32_t *)(d + o_block);
+    v.count = (const uint16_t *)(d + o_count);
     if (e == hipSuccess) e = launch_shg_prep(v, dw, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -1213,7 +1235,15 @@ soc_status soc_shg_solve(soc_ctx c, soc_grid g, soc_shg_model m, const double *d
     a.absorbed = d_absorbed;
     a.emission = d_emission;
     a.P = d_P;
-    HIPCHK(c, launch_shg(a, c->stream));
+    // the size parts' emissions need scratch; where it cannot be had (it
+    // would grow inside a graph capture, or memory is short), one part
+    int parts = shg_parts(g->ncells, m->S);
+    if (parts > 1) {
+        const int64_t need = (int64_t)parts * m->K * g->ncells;
+        if ((c->capturing && need > c->cap_shg) || grow(c, &c->d_shg, c->cap_shg, need) != SOC_OK) parts = 1;
+        a.part = c->d_shg;
+    }
+    HIPCHK(c, launch_shg(a, parts, c->stream));
     return SOC_OK;
 }
 

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace soc {
 
 // Private copies of a tally for the Monte Carlo launches: two per XCD, so
@@ -117,14 +119,28 @@ struct ShgModelDev {
     const double *abundance;            // [S] grains per H
     const double *sigma;                // [S][K] cm^2 per grain
     const double *U, *T;                // [S][N]
-    double *share;                      // [S][K] share of each size in the absorption of band k
-    double *emit;                       // [S][N][K] 4 pi sigma B_nu(T_i)
+    double *rate;                       // [S][K padded to 64 or 128] photon rate per grain and absorbed energy per H
+    double *first;                      // matrix of the first bucket, tiled (shg_prep_kernel)
+    double *emit;                       // matrix of the emission, tiled
     double *icool;                      // [S][N] inverse cooling rate from bin i to i-1: (U_i - U_i-1) / L(T_i)
-    double *idu;                        // [S][N] 1 / (U_i - U_i-1), 0 at i = 0
-    uint8_t *ks;                        // [S][ks stride] ks[j][i] (j, i < N): photons k < ks of bin i land below
-                                        // bin j (K at j = N-1); 16-byte aligned, each size padded to 16 bytes
-    int32_t *band;                      // [S] up[j][i] = 0 for j - i >= band
+    const uint16_t *count;              // [S][N] groups of the stream in step j
+    const int32_t *first_block;         // [S] the size's first block of the stream
+    const uint32_t *stream;             // shg_build_stream
 };
+// A product's operand sizes: 16-row tiles and 8-entry reduction steps of a
+// dimension of n photons or bins, padded to 64 or 128.
+__host__ __device__ inline int shg_steps(int n) { return n > 64 ? 16 : 8; }
+__host__ __device__ inline int shg_tiles(int n) { return shg_steps(n) / 2; }
+constexpr int kShgRow = 16 * 8;         // bytes of one LDS row (16 cells)
+// LDS row of suffix sum r (shg.hip)
+__host__ __device__ constexpr int shg_sr_place(int r) { return (r & ~3) | ((r & 1) << 1) | ((r >> 1) & 1); }
+// The coefficient stream of a model (host).
+struct ShgStream {
+    std::vector<uint16_t> count;
+    std::vector<int32_t> first_block;
+    std::vector<uint32_t> words;
+};
+void shg_build_stream(int S, int K, int N, const double *hnu, const double *U, ShgStream &out);
 struct ShgArgs {
     ShgModelDev model;
     const uint32_t *words;
@@ -135,14 +151,12 @@ struct ShgArgs {
     const double *absorbed;             // [K][ncells]
     double *emission;                   // [K][ncells]
     double *P;                          // [ncells][S][N] or NULL
+    double *part;                       // emissions of the size parts
 };
-// bytes of one size's ks table, a multiple of 16 for vector copies
-__host__ __device__ inline int shg_ks_stride(int N)
-{
-    return (N * N + 15) & ~15;
-}
 hipError_t launch_shg_prep(const ShgModelDev &m, const double *w, hipStream_t s);
-hipError_t launch_shg(const ShgArgs &a, hipStream_t s);
+int shg_parts(int64_t ncells, int S);
+// parts: size parts (1, or as a.part holds: parts x K x ncells doubles)
+hipError_t launch_shg(const ShgArgs &a, int parts, hipStream_t s);
 
 struct SegmentDev {
     int64_t cell;
