@@ -139,7 +139,7 @@ struct soc_temp_table_s {
     double T_floor = 0.0, T_max = 0.0, lnTf = 0.0, dlnT = 0.0;
     double *d_lnG = nullptr;
     double G0 = 0.0, Gn = 0.0, start_scale = 0.0;   // the table's ends; its search (TempArgs)
-    uint16_t *d_start = nullptr;
+    uint16_t *d_start = nullptr;                    // after the table in the same allocation
 };
 
 struct soc_shg_model_s {
@@ -1340,14 +1340,15 @@ soc_status soc_temp_table_build(soc_ctx c, int32_t K, const double *nu, const do
         if (r != SOC_OK) soc_temp_table_destroy(t);
         return r;
     };
-    if (hipMalloc((void **)&t->d_lnG, sizeof(double) * nT) != hipSuccess ||
+    if (hipMalloc((void **)&t->d_lnG, sizeof(double) * nT + sizeof(uint16_t) * kTempStarts) != hipSuccess ||
         hipMalloc((void **)&d_f, sizeof(double) * 3 * K) != hipSuccess)
         return cleanup(fail(c, SOC_ENOMEM, "temperature table"));
     if (hipMemcpyAsync(d_f, nu, sizeof(double) * K, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemcpyAsync(d_f + K, w_nu, sizeof(double) * K, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemcpyAsync(d_f + 2 * K, sigma_abs, sizeof(double) * K, hipMemcpyHostToDevice, c->stream) != hipSuccess)
         return cleanup(fail(c, SOC_EHIP, "table upload"));
-    if (launch_temp_table(d_f, d_f + K, d_f + 2 * K, K, t->lnTf, t->dlnT, nT, t->d_lnG, c->stream) != hipSuccess)
+    t->d_start = (uint16_t *)(t->d_lnG + nT);
+    if (launch_temp_table(d_f, d_f + K, d_f + 2 * K, K, t->lnTf, t->dlnT, nT, t->d_lnG, t->d_start, c->stream) != hipSuccess)
         return cleanup(fail(c, SOC_EHIP, "table launch"));
     std::vector<double> h(nT);
     if (hipMemcpyAsync(h.data(), t->d_lnG, sizeof(double) * nT, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
@@ -1357,23 +1358,9 @@ soc_status soc_temp_table_build(soc_ctx c, int32_t K, const double *nu, const do
         if (!std::isfinite(h[j]) || (j > 0 && !(h[j] > h[j - 1])))
             return cleanup(fail(c, SOC_EINVAL, "Gamma(T) is not finite and increasing on [T_floor, T_max] (bin %d)", j));
     }
-    // search starts: the last entry safely below each of kTempStarts equal
-    // steps of ln Gamma (the margins cover the rounding of the edge and of
-    // the device's step number)
     t->G0 = h.front();
     t->Gn = h.back();
     t->start_scale = kTempStarts / (t->Gn - t->G0);
-    std::vector<uint16_t> start(kTempStarts);
-    for (int b = 0, lo = 0; b < kTempStarts; ++b) {
-        const double edge = t->G0 + (b - 1e-9) / t->start_scale - 1e-15 * (std::fabs(t->G0) + std::fabs(t->Gn));
-        while (lo + 2 < nT && h[lo + 1] <= edge) ++lo;
-        start[b] = (uint16_t)lo;
-    }
-    if (hipMalloc((void **)&t->d_start, sizeof(uint16_t) * kTempStarts) != hipSuccess)
-        return cleanup(fail(c, SOC_ENOMEM, "temperature table"));
-    if (hipMemcpyAsync(t->d_start, start.data(), sizeof(uint16_t) * kTempStarts, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess)
-        return cleanup(fail(c, SOC_EHIP, "table upload"));
     *out = t;
     return cleanup(SOC_OK);
 }
@@ -1383,7 +1370,6 @@ void soc_temp_table_destroy(soc_temp_table t)
     if (!t) return;
     (void)hipSetDevice(t->device);
     (void)hipFree(t->d_lnG);
-    (void)hipFree(t->d_start);
     delete t;
 }
 

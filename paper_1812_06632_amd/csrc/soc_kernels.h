@@ -272,7 +272,7 @@ hipError_t launch_leaf_list(const uint32_t *words, int64_t ncells, int64_t *scan
 
 // temperature
 hipError_t launch_temp_table(const double *nu, const double *w, const double *sabs, int32_t K, double lnTf,
-                             double dlnT, int32_t nT, double *lnG, hipStream_t s);
+                             double dlnT, int32_t nT, double *lnG, uint16_t *start, hipStream_t s);
 struct TempArgs {
     const uint32_t *words;
     int64_t ncells;

@@ -34,10 +34,28 @@ __global__ void temp_table_kernel(const double *nu, const double *w, const doubl
     lnG[j] = log(12.566370614359172 * s);
 }
 
+// Search starts: for each of kTempStarts equal steps of ln Gamma the last
+// entry safely below the step's lower edge (the margins cover the rounding
+// of the edge and of the solve's step number), at most nT - 2.
+__global__ void temp_starts_kernel(const double *lnG, int32_t nT, uint16_t *start)
+{
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= kTempStarts) return;
+    const double G0 = lnG[0], Gn = lnG[nT - 1];
+    const double edge = G0 + (b - 1e-9) * ((Gn - G0) / kTempStarts) - 1e-15 * (fabs(G0) + fabs(Gn));
+    int lo = 0, hi = nT - 1;   // lnG[lo] <= edge (or lo == 0), lnG[hi] > edge
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (lnG[mid] <= edge) lo = mid; else hi = mid;
+    }
+    start[b] = (uint16_t)lo;
+}
+
 hipError_t launch_temp_table(const double *nu, const double *w, const double *sabs, int32_t K, double lnTf,
-                             double dlnT, int32_t nT, double *lnG, hipStream_t s)
+                             double dlnT, int32_t nT, double *lnG, uint16_t *start, hipStream_t s)
 {
     hipLaunchKernelGGL(temp_table_kernel, dim3((nT + 255) / 256), dim3(256), 0, s, nu, w, sabs, K, lnTf, dlnT, nT, lnG);
+    hipLaunchKernelGGL(temp_starts_kernel, dim3(kTempStarts / 256), dim3(256), 0, s, (const double *)lnG, nT, start);
     return hipGetLastError();
 }
 
