@@ -40,8 +40,8 @@ struct Layer {
     int32_t level_in = 0, level_out = 0;
     int64_t w_off = 0, b_off = 0;    // offsets in the parameter array
     int64_t nw = 0;
-    uint16_t *wf = nullptr;          // forward weights, [phase][npad_f][taps * cin_buf]
-    uint16_t *wb = nullptr;          // backward-data weights, [phase][npad_b][taps * cout_buf]
+    uint16_t *wf = nullptr;          // forward weights in operand order (weight_operand), npad_f x taps * cin_buf per phase
+    uint16_t *wb = nullptr;          // backward-data weights, npad_b x taps * cout_buf per phase
     int32_t npad_f = 0, npad_b = 0;
 };
 

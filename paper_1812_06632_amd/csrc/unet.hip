@@ -14,10 +14,10 @@
 //
 // Each wave computes a 32-row x 32*NT-column tile with
 // v_mfma_f32_32x32x16_bf16 (8 BF16 of A and B per lane, 16 FP32 results
-// per lane); operands are loaded straight from channels-last tensors as
-// 16-byte vectors: 8 consecutive input channels of one position (A) and 8
-// consecutive reduction entries of one output channel (B, weights stored
-// output-channel-major).  The epilogue adds the bias, applies the leaky
+// per lane); operands are 16-byte vectors per lane: 8 consecutive input
+// channels of one position of a channels-last tensor (A) and 8 consecutive
+// reduction entries of one output channel (B, the weights laid out in
+// operand order).  The epilogue adds the bias, applies the leaky
 // ReLU, or -- in backward-data passes -- multiplies by the leaky ReLU
 // derivative taken from the sign of the stored activation and adds a
 // second gradient (the skip connection), then rounds to BF16.
@@ -31,6 +31,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "unet.h"
 
@@ -79,7 +80,7 @@ struct ConvArgs {
     int32_t k, s_in, pad;           // taps per axis, input stride, padding
     int32_t nph, s_out;             // output phases (1 or 8), output stride
     int32_t oz, oy, ox;             // output grid of one sample
-    const uint16_t *w;              // [nph][npad][k^3 * cin]
+    const uint16_t *w;              // weight operands, see weight_operand
     int32_t npad;
     const float *bias;              // NULL: none
     int32_t cout;                   // columns stored (n < cout)
@@ -94,9 +95,82 @@ struct ConvArgs {
     int32_t yf_cs;
 };
 
+// A weight operand (B) of one product: 32 output channels x 16 input
+// channels of one tap as the 64 lanes hold them (lane l: channel l mod 32,
+// entries 8 (l / 32) .. + 7), 1 KB in a row: [phase][tile of 32 output
+// channels][tap][16 input channels][lane][8].  Read from rows of a
+// [output channel][tap][input channel] array, a load took 32 bytes from each
+// of 32 cache lines.
+__device__ inline bf16x8_t weight_operand(const ConvArgs &a, int ph, int ntile, int tap, int c, int lane)
+{
+    const int taps = a.k * a.k * a.k;
+    const size_t f = ((size_t)(ph * (a.npad / 32) + ntile) * taps + tap) * (a.cin / 16) + c / 16;
+    return ld8(a.w + f * 512 + (uint32_t)lane * 8u);
+}
+
+// Epilogue of one 32 x 32 tile of a wave (lane l: column n0 + l mod 32, rows
+// 8 (v / 4) + 4 (l / 32) + v % 4): bias and leaky ReLU, or the leaky ReLU
+// derivative and the second gradient, then the store.  The tile goes through
+// the wave's own kTileWords words of LDS, so that a lane then holds 8
+// channels of one row and the tensors are read and written 16 bytes at a time
+// (channels come in multiples of 16); two bytes at a time, the epilogue took
+// as long as the products.  position(row, op): the row's output position;
+// false outside the grid.
+constexpr int kTileRow = 40;   // words per row: rows 4 apart (a write's two halves) on different banks
+constexpr int kTileWords = 32 * kTileRow;
+
+template <typename F>
+__device__ __forceinline__ void store_tile(const ConvArgs &a, float *tile, const f32x16_t &acc, int n0, int lane, F position)
+{
+    const int half = lane >> 5, r = lane & 31;
+    const float bias = a.bias && n0 + r < a.cout ? a.bias[n0 + r] : 0.0f;
+    __builtin_amdgcn_wave_barrier();   // the tile before has been read
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        float val = acc[v];
+        if (a.bias) val += bias;
+        if (a.act) val = val > 0.0f ? val : kLeak * val;
+        tile[(8 * (v >> 2) + 4 * half + (v & 3)) * kTileRow + r] = val;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (!a.y) {   // FP32 output of a few channels
+        for (int i = lane; i < 32 * a.cout; i += 64) {
+            size_t op;
+            if (position(i / a.cout, op)) a.yf[op * a.yf_cs + i % a.cout] = tile[(i / a.cout) * kTileRow + i % a.cout];
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = (lane >> 2) + 16 * i, n = n0 + 8 * (lane & 3);
+        size_t op;
+        if (!position(row, op) || n >= a.cout) continue;
+        float val[8];
+        *reinterpret_cast<u32x4 *>(val) = *reinterpret_cast<const u32x4 *>(tile + row * kTileRow + 8 * (lane & 3));
+        *reinterpret_cast<u32x4 *>(val + 4) = *reinterpret_cast<const u32x4 *>(tile + row * kTileRow + 8 * (lane & 3) + 4);
+        uint16_t h[8];
+        if (a.slope) {
+            *reinterpret_cast<u32x4 *>(h) = *reinterpret_cast<const u32x4 *>(a.slope + op * a.sl_cs + a.sl_co + n);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (!(bf2f(h[j]) > 0.0f)) val[j] *= kLeak;
+        }
+        if (a.add) {
+            *reinterpret_cast<u32x4 *>(h) = *reinterpret_cast<const u32x4 *>(a.add + op * a.ad_cs + a.ad_co + n);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) val[j] += bf2f(h[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) h[j] = f2bf(val[j]);
+        *reinterpret_cast<u32x4 *>(a.y + op * a.y_cs + a.y_co + n) = *reinterpret_cast<const u32x4 *>(h);
+    }
+}
+
 template <int NT>
 __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
 {
+    __shared__ __attribute__((aligned(16))) float tiles[4][kTileWords];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int half = lane >> 5;
@@ -120,11 +194,6 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
         qz = t % a.mz;
         b = t / a.mz;
     }
-    const int K = a.k * a.k * a.k * a.cin;
-    const uint16_t *wrow[NT];
-#pragma unroll
-    for (int s = 0; s < NT; ++s) wrow[s] = a.w + (size_t)(ph * a.npad + n0 + 32 * s + r) * K + 8 * half;
-
     f32x16_t acc[NT];
 #pragma unroll
     for (int s = 0; s < NT; ++s)
@@ -141,288 +210,226 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
                 const uint16_t *xrow =
                     ok ? a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + 8 * half
                        : nullptr;
-                const int kb = tap * a.cin;
                 for (int c = 0; c < a.cin; c += 16) {
                     const bf16x8_t A = ok ? ld8(xrow + c) : zero8();
 #pragma unroll
                     for (int s = 0; s < NT; ++s) {
-                        const bf16x8_t B = ld8(wrow[s] + kb + c);
+                        const bf16x8_t B = weight_operand(a, ph, n0 / 32 + s, tap, c, lane);
                         acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[s], 0, 0, 0);
                     }
                 }
             }
 
-    // epilogue: lane holds column n0 + 32 s + r and rows 8 (v / 4) + 4 half + v % 4
     const int ez = (ph >> 2) & 1, ey = (ph >> 1) & 1, ex = ph & 1;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const uint32_t row = tile + 8 * (v >> 2) + 4 * half + (v & 3);
-        if (row >= mtot) continue;
-        uint32_t t = row;
-        const int px = t % a.mx;
-        t /= a.mx;
-        const int py = t % a.my;
-        t /= a.my;
-        const int pz = t % a.mz;
-        const int pb = t / a.mz;
-        const size_t op =
-            (size_t)((pb * a.oz + a.s_out * pz + ez) * a.oy + a.s_out * py + ey) * a.ox + a.s_out * px + ex;
-#pragma unroll
-        for (int s = 0; s < NT; ++s) {
-            const int n = n0 + 32 * s + r;
-            if (n >= a.cout) continue;
-            float val = acc[s][v];
-            if (a.bias) val += a.bias[n];
-            if (a.act) val = val > 0.0f ? val : kLeak * val;
-            if (a.slope && !(bf2f(a.slope[op * a.sl_cs + a.sl_co + n]) > 0.0f)) val *= kLeak;
-            if (a.add) val += bf2f(a.add[op * a.ad_cs + a.ad_co + n]);
-            if (a.y)
-                a.y[op * a.y_cs + a.y_co + n] = f2bf(val);
-            else
-                a.yf[op * a.yf_cs + n] = val;
-        }
-    }
+    for (int s = 0; s < NT; ++s)
+        store_tile(a, tiles[wave], acc[s], n0 + 32 * s, lane, [&](int i, size_t &op) {
+            uint32_t t = tile + i;
+            if (t >= mtot) return false;
+            const int px = t % a.mx;
+            t /= a.mx;
+            const int py = t % a.my;
+            t /= a.my;
+            const int pz = t % a.mz;
+            const int pb = t / a.mz;
+            op = (size_t)((pb * a.oz + a.s_out * pz + ez) * a.oy + a.s_out * py + ey) * a.ox + a.s_out * px + ex;
+            return true;
+        });
 }
 
 // 3^3 convolutions (stride 1, padding 1) -- most of the network's work --
-// with the input staged in LDS: a workgroup owns a 4 x 8 x 8 brick of
-// output positions (256 rows); for every chunk of 32 input channels it
-// loads the 6 x 10 x 10 halo of the brick once (zero outside the volume)
-// and all 27 taps read their A fragments from LDS.  Each wave computes two
-// 32-row tiles (half z-planes of the brick) x 32*NT columns, so every B
-// fragment, shared by the four waves through L1, feeds two MFMAs.
-constexpr int kBZ = 4, kBY = 8, kBX = 8;
-constexpr int kHZ = kBZ + 2, kHY = kBY + 2, kHX = kBX + 2;
-constexpr int kHalo = kHZ * kHY * kHX;   // 600 positions
-constexpr int kCC = 32;                  // input channels per LDS chunk
-constexpr int kHS = kCC + 8;             // padded position stride in the halo (elements)
+// with the input staged in LDS.  A workgroup owns a brick of Z x 8 x 8 output
+// positions and NC tiles of 32 columns; its 2 NC waves are the brick's two
+// y-halves times the column tiles, and a wave computes Z 32-row tiles (4 x 8
+// positions of one z-plane each) of its columns.  For every chunk of CC input
+// channels the workgroup loads the (Z + 2) x 10 x 10 halo of the brick (zero
+// outside the volume).
+//
+// A tap row (ty, tx) of one input plane is the A operand of up to three
+// output planes (tz = 0, 1, 2), so a wave walks the input planes and reads
+// each operand from LDS once for three products: (Z + 2) / (3 Z) reads per
+// product.  The 27 weight operands of a chunk stay in registers; each is
+// reloaded for the next chunk right after its last use, a chunk ahead of its
+// next.  An output's products come in the order chunk, tz, ty, tx, channel,
+// whatever Z.
+//
+// A halo position is 16 channels (32 bytes, two 16-byte units) and a halo
+// row of 10 positions is padded to 21 units: the 16 lanes of an operand read
+// that the LDS serves together (two x-rows of 8 positions) then fall on 16
+// different units of a 256-byte window, the even ones for one row and the
+// odd ones for the other, so the reads are free of bank conflicts.  Chunks
+// of 32 channels are two such planes.
+//
+// Measured, one sample of 64^3, base 32, four levels (122 GFLOP, 0.11 ms at
+// the rate of a large BF16 matrix product): forward 1.21 ms before (each
+// operand read from LDS for one product, weights in rows, two-byte epilogue),
+// 0.43 ms now.  What is left is the latency of a chunk on the small grids (a
+// wave per SIMD or less) and, on the large ones, the halo loads between two
+// barriers with two waves per SIMD.
+constexpr int kH3 = 10;                       // halo edge in y and x
+constexpr int kRow3 = kH3 * 16 + 8;           // 168 elements per halo row: an odd number of 16-byte units
 
-template <int NT>
-__global__ __launch_bounds__(256) void conv3_lds_kernel(ConvArgs a)
+template <int Z, int CC, int NC>
+__global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_kernel(ConvArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t halo[kHalo * kHS];
+    constexpr int kThreads = 128 * NC, kHalf = CC / 16;
+    constexpr int kPlane = (Z + 2) * kH3 * kRow3;                // elements of 16 channels of the halo
+    // the halo's rows of 10 positions: kUnits 16-byte units each, kRowsAt
+    // rows at a time
+    constexpr int kUnits = kH3 * (CC / 8), kRows = (Z + 2) * kH3;
+    constexpr int kRowsAt = kThreads / kUnits, kPer = (kRows + kRowsAt - 1) / kRowsAt;
+    constexpr bool kAhead = Z < 4;   // few workgroups: the next halo is loaded during the products
+    constexpr int kTiles = 2 * 2 * NC * kTileWords;   // the epilogue's tiles, in elements of the halo
+    __shared__ __attribute__((aligned(16))) uint16_t halo[kHalf * kPlane > kTiles ? kHalf * kPlane : kTiles];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int half = lane >> 5;
     const int r = lane & 31;
-    const int nbx = (a.mx + kBX - 1) / kBX, nby = (a.my + kBY - 1) / kBY, nbz = (a.mz + kBZ - 1) / kBZ;
+    const int nbx = (a.mx + 7) / 8, nby = (a.my + 7) / 8, nbz = (a.mz + Z - 1) / Z;
+    // neighbouring bricks share halos: consecutive ones on one XCD (its
+    // workgroups are every eighth)
     int bid = blockIdx.x;
+    if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
     const int bxi = bid % nbx;
     bid /= nbx;
     const int byi = bid % nby;
     bid /= nby;
     const int bzi = bid % nbz;
     const int b = bid / nbz;
-    const int z0 = bzi * kBZ, y0 = byi * kBY, x0 = bxi * kBX;
-    const int n0 = blockIdx.y * 32 * NT;
-    const int K = 27 * a.cin;
+    const int z0 = bzi * Z, y0 = byi * 8, x0 = bxi * 8;
+    const int n0 = (blockIdx.y * NC + (wave >> 1)) * 32;
+    const int ly = (wave & 1) * 4 + (r >> 3), lx = r & 7;
+    const uint16_t *const arow = halo + ly * kRow3 + lx * 16 + 8 * half;
+    const int ntile = __builtin_amdgcn_readfirstlane(n0 / 32);
+    const uint16_t *const wtile = a.w + (size_t)ntile * 27 * a.cin * 32;
+    const auto weights = [&](int t, int c) { return ld8(wtile + (size_t)(t * (a.cin / 16) + c / 16) * 512 + (uint32_t)lane * 8u); };
 
-    // this lane's two rows (row tiles 2 wave and 2 wave + 1 of the brick)
-    int lz[2], ly[2];
-    const int lx = r & 7;
+    // this lane's unit of a halo row and its first row
+    const int unit = tid % kUnits, row0 = tid / kUnits;
+    const int hx = unit / (CC / 8), hg = unit % (CC / 8);
+    const int xx = x0 + hx - 1;
+    const bool in_x = row0 < kRowsAt && xx >= 0 && xx < a.ix;
+    uint16_t *const hdst = halo + (hg >> 1) * kPlane + row0 * kRow3 + hx * 16 + 8 * (hg & 1);
+    const auto load_row = [&](int first, int e, int c0) {
+        const int row = first + kRowsAt * e;
+        const int zz = z0 + row / kH3 - 1, yy = y0 + row % kH3 - 1;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (in_x && row < kRows && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && c0 + 8 * hg < a.cin)
+            v = *reinterpret_cast<const u32x4 *>(
+                a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + c0 + 8 * hg);
+        return v;
+    };
+    const auto store_row = [&](int e, u32x4 v) {
+        if (row0 < kRowsAt && row0 + kRowsAt * e < kRows) *reinterpret_cast<u32x4 *>(hdst + kRowsAt * e * kRow3) = v;
+    };
+    u32x4 ph[kAhead ? kPer : 1];
+    const auto load_halo = [&](int c0) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int rt = 2 * wave + t;
-        lz[t] = rt >> 1;
-        ly[t] = (rt & 1) * 4 + (r >> 3);
-    }
-    const uint16_t *wrow[NT];
-#pragma unroll
-    for (int s = 0; s < NT; ++s) wrow[s] = a.w + (size_t)(n0 + 32 * s + r) * K + 8 * half;
+        for (int e = 0; e < kPer; ++e) ph[e] = load_row(row0, e, c0);
+    };
 
-    f32x16_t acc[2][NT];
+    f32x16_t acc[Z];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int z = 0; z < Z; ++z)
+        for (int v = 0; v < 16; ++v) acc[z][v] = 0.0f;
+    bf16x8_t B[27][kHalf];
 #pragma unroll
-        for (int s = 0; s < NT; ++s)
-            for (int v = 0; v < 16; ++v) acc[t][s][v] = 0.0f;
+    for (int t = 0; t < 27; ++t)
+#pragma unroll
+        for (int h = 0; h < kHalf; ++h) B[t][h] = h == 0 || a.cin > 16 ? weights(t, 16 * h) : zero8();
 
-    for (int c0 = 0; c0 < a.cin; c0 += kCC) {
-        const int cc = min(kCC, a.cin - c0);   // 16 or 32
-        const int groups = cc >> 3;
-        __syncthreads();   // the previous chunk has been consumed
-        for (int i = tid; i < kHalo * groups; i += 256) {
-            const int pos = i / groups, g = i - pos * groups;
-            const int hx = pos % kHX, hy = (pos / kHX) % kHY, hz = pos / (kHX * kHY);
-            const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && xx >= 0 && xx < a.ix)
-                v = *reinterpret_cast<const u32x4 *>(
-                    a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + c0 + 8 * g);
-            *reinterpret_cast<u32x4 *>(&halo[pos * kHS + 8 * g]) = v;
+    // products of one chunk; kNext: another one follows, its weights are loaded
+    const auto chunk = [&](auto has_next, int c0) {
+        constexpr bool kNext = decltype(has_next)::value;
+        const int cn = c0 + CC;
+        // operand (p, t) of the halo: input plane p, tap row and column t
+        const auto operand = [&](int i, int h) {
+            return ld8(arow + h * kPlane + ((i / 9) * kH3 + (i % 9) / 3) * kRow3 + (i % 3) * 16);
+        };
+        constexpr int kOps = 9 * (Z + 2);
+        bf16x8_t A[3][kHalf];   // two operands are read ahead
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int h = 0; h < kHalf; ++h) A[i][h] = operand(i, h);
+#pragma unroll
+        for (int i = 0; i < kOps; ++i) {
+            const int p = i / 9, t = i % 9;
+            if (i + 2 < kOps)
+#pragma unroll
+                for (int h = 0; h < kHalf; ++h) A[(i + 2) % 3][h] = operand(i + 2, h);
+#pragma unroll
+            for (int tz = 0; tz < 3; ++tz) {
+                const int z = p - tz;
+                if (z < 0 || z >= Z) continue;
+#pragma unroll
+                for (int h = 0; h < kHalf; ++h)
+                    acc[z] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[i % 3][h], B[9 * tz + t][h], acc[z], 0, 0, 0);
+                if (kNext && z == Z - 1)
+#pragma unroll
+                    for (int h = 0; h < kHalf; ++h)
+                        B[9 * tz + t][h] = h == 0 || cn + 16 < a.cin ? weights(9 * tz + t, cn + 16 * h) : zero8();
+            }
+            __builtin_amdgcn_sched_barrier(0);   // or the scheduler reads all operands at once and spills
         }
-        __syncthreads();
-        int tap = 0;
-        for (int tz = 0; tz < 3; ++tz)
-            for (int ty = 0; ty < 3; ++ty)
-                for (int tx = 0; tx < 3; ++tx, ++tap) {
-                    const int h0 = ((lz[0] + tz) * kHY + ly[0] + ty) * kHX + lx + tx;
-                    const int h1 = ((lz[1] + tz) * kHY + ly[1] + ty) * kHX + lx + tx;
-                    const int kb = tap * a.cin + c0;
-                    for (int cg = 0; cg < cc; cg += 16) {
-                        const bf16x8_t A0 =
-                            __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4 *>(&halo[h0 * kHS + cg + 8 * half]));
-                        const bf16x8_t A1 =
-                            __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4 *>(&halo[h1 * kHS + cg + 8 * half]));
+    };
+    if (kAhead) load_halo(0);
+    for (int c0 = 0; c0 < a.cin; c0 += CC) {
+        __syncthreads();   // the previous chunk has been consumed
+        if (kAhead) {
 #pragma unroll
-                        for (int s = 0; s < NT; ++s) {
-                            const bf16x8_t B = ld8(wrow[s] + kb + cg);
-                            acc[0][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A0, B, acc[0][s], 0, 0, 0);
-                            acc[1][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, B, acc[1][s], 0, 0, 0);
-                        }
-                    }
-                }
-    }
-
-    // epilogue: lane holds column n0 + 32 s + r and, in row tile t, the rows
-    // 8 (v / 4) + 4 half + v % 4 (= 8 y-rows of 8 x in brick order)
+            for (int e = 0; e < kPer; ++e) store_row(e, ph[e]);
+        } else {
+            constexpr int kBatch = 5;   // rows in flight per lane
+            int first = row0;           // as if new in every chunk: addresses kept from chunk to chunk would spill
+            asm volatile("" : "+v"(first));
+            static_assert(kAhead || kPer % kBatch == 0, "rows come in batches");
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int rt = 2 * wave + t;
+            for (int e0 = 0; e0 < kPer; e0 += kBatch) {
+                u32x4 v[kBatch];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = 8 * (v >> 2) + 4 * half + (v & 3);   // 0..31 within the tile
-            const int pz = z0 + (rt >> 1), py = y0 + (rt & 1) * 4 + (row >> 3), px = x0 + (row & 7);
-            if (pz >= a.mz || py >= a.my || px >= a.mx) continue;
-            const size_t op = (size_t)((b * a.oz + pz) * a.oy + py) * a.ox + px;
+                for (int e = 0; e < kBatch; ++e) v[e] = load_row(first, e0 + e, c0);
 #pragma unroll
-            for (int s = 0; s < NT; ++s) {
-                const int n = n0 + 32 * s + r;
-                if (n >= a.cout) continue;
-                float val = acc[t][s][v];
-                if (a.bias) val += a.bias[n];
-                if (a.act) val = val > 0.0f ? val : kLeak * val;
-                if (a.slope && !(bf2f(a.slope[op * a.sl_cs + a.sl_co + n]) > 0.0f)) val *= kLeak;
-                if (a.add) val += bf2f(a.add[op * a.ad_cs + a.ad_co + n]);
-                if (a.y)
-                    a.y[op * a.y_cs + a.y_co + n] = f2bf(val);
-                else
-                    a.yf[op * a.yf_cs + n] = val;
+                for (int e = 0; e < kBatch; ++e) store_row(e0 + e, v[e]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __syncthreads();
+        if (c0 + CC < a.cin) {
+            if (kAhead) load_halo(c0 + CC);
+            chunk(std::true_type{}, c0);
+        } else {
+            chunk(std::false_type{}, c0);
+        }
     }
+
+    __syncthreads();   // the halo has been consumed: its LDS holds the tiles
+    float *const tile = reinterpret_cast<float *>(halo) + wave * kTileWords;
+#pragma unroll
+    for (int z = 0; z < Z; ++z)
+        store_tile(a, tile, acc[z], n0, lane, [&](int i, size_t &op) {
+            const int pz = z0 + z, py = y0 + (wave & 1) * 4 + (i >> 3), px = x0 + (i & 7);
+            op = (size_t)((b * a.oz + pz) * a.oy + py) * a.ox + px;
+            return pz < a.mz && py < a.my && px < a.mx;
+        });
 }
 
-// The same 3^3 convolution for large grids: an 8 x 8 x 8 brick per
-// workgroup (512 rows, halo 10^3 = 1.95x instead of 2.34x), 16 input
-// channels per LDS chunk, and four 32-row tiles per wave (two z-planes),
-// so every B fragment feeds four MFMAs per column tile.  The x-taps and
-// the per-tap channel groups are unrolled so that the weight loads of a
-// tap row are issued before its MFMAs.  A halo position is its 16
-// channels (32 bytes, two 16-byte units) and a halo row of 10 positions
-// is padded to 21 units: the 16 lanes of an operand read that the LDS
-// serves together (two x-rows of 8 positions) then fall on 16 different
-// units of a 256-byte window, the even ones for one row and the odd ones
-// for the other, so the reads are free of bank conflicts; the halo takes
-// 33.6 KB, and with at most 128 registers four workgroups share a CU.
-constexpr int kB3 = 8;
-constexpr int kH3 = kB3 + 2;             // 10
-constexpr int kHalo3 = kH3 * kH3 * kH3;  // 1000 positions
-constexpr int kCC3 = 16;                 // 32 bytes per position, unpadded
-constexpr int kRow3 = kH3 * kCC3 + 8;    // 168 elements per halo row: an odd number of 16-byte units
-
-template <int NT>
-__global__ __launch_bounds__(256, 4) void conv3_big_kernel(ConvArgs a)
+template <int CC, int NC>
+static void launch_conv3_as(const ConvArgs &a, hipStream_t s)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t halo[kH3 * kH3 * kRow3];   // 33600 B
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int half = lane >> 5;
-    const int r = lane & 31;
-    const int nbx = (a.mx + kB3 - 1) / kB3, nby = (a.my + kB3 - 1) / kB3, nbz = (a.mz + kB3 - 1) / kB3;
-    int bid = blockIdx.x;
-    const int bxi = bid % nbx;
-    bid /= nbx;
-    const int byi = bid % nby;
-    bid /= nby;
-    const int bzi = bid % nbz;
-    const int b = bid / nbz;
-    const int z0 = bzi * kB3, y0 = byi * kB3, x0 = bxi * kB3;
-    const int n0 = blockIdx.y * 32 * NT;
-    const int K = 27 * a.cin;
-
-    // row tile t of this wave: z-plane 2 wave + t / 2, y-rows 4 (t % 2) .. +3, x = r % 8
-    const int lx = r & 7;
-    int hbase[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int lz = 2 * wave + (t >> 1), ly = (t & 1) * 4 + (r >> 3);
-        hbase[t] = (lz * kH3 + ly) * kRow3 + lx * kCC3 + 8 * half;
-    }
-    const uint16_t *wrow[NT];
-#pragma unroll
-    for (int s = 0; s < NT; ++s) wrow[s] = a.w + (size_t)(n0 + 32 * s + r) * K + 8 * half;
-
-    f32x16_t acc[4][NT];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int s = 0; s < NT; ++s)
-            for (int v = 0; v < 16; ++v) acc[t][s][v] = 0.0f;
-
-    for (int c0 = 0; c0 < a.cin; c0 += kCC3) {
-        __syncthreads();   // the previous chunk has been consumed
-        for (int i = tid; i < kHalo3 * 2; i += 256) {
-            const int pos = i >> 1, g = i & 1;
-            const int hx = pos % kH3, hy = (pos / kH3) % kH3, hz = pos / (kH3 * kH3);
-            const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && xx >= 0 && xx < a.ix)
-                v = *reinterpret_cast<const u32x4 *>(
-                    a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + c0 + 8 * g);
-            *reinterpret_cast<u32x4 *>(&halo[(hz * kH3 + hy) * kRow3 + hx * kCC3 + 8 * g]) = v;
-        }
-        __syncthreads();
-        for (int tzy = 0; tzy < 9; ++tzy) {
-            const int tz = tzy / 3, ty = tzy % 3;
-            const int hoff = (tz * kH3 + ty) * kRow3;
-            bf16x8_t B[3][NT];
-#pragma unroll
-            for (int tx = 0; tx < 3; ++tx)
-#pragma unroll
-                for (int s = 0; s < NT; ++s) B[tx][s] = ld8(wrow[s] + (tzy * 3 + tx) * a.cin + c0);
-#pragma unroll
-            for (int tx = 0; tx < 3; ++tx) {
-                bf16x8_t A[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    A[t] = __builtin_bit_cast(
-                        bf16x8_t, *reinterpret_cast<const u32x4 *>(&halo[hbase[t] + hoff + tx * kCC3]));
-#pragma unroll
-                for (int s = 0; s < NT; ++s)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        acc[t][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t], B[tx][s], acc[t][s], 0, 0, 0);
-            }
-        }
-    }
-
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = 8 * (v >> 2) + 4 * half + (v & 3);   // 0..31 within the tile: 4 y-rows of 8
-            const int pz = z0 + 2 * wave + (t >> 1), py = y0 + (t & 1) * 4 + (row >> 3), px = x0 + (row & 7);
-            if (pz >= a.mz || py >= a.my || px >= a.mx) continue;
-            const size_t op = (size_t)((b * a.oz + pz) * a.oy + py) * a.ox + px;
-#pragma unroll
-            for (int s = 0; s < NT; ++s) {
-                const int n = n0 + 32 * s + r;
-                if (n >= a.cout) continue;
-                float val = acc[t][s][v];
-                if (a.bias) val += a.bias[n];
-                if (a.act) val = val > 0.0f ? val : kLeak * val;
-                if (a.slope && !(bf2f(a.slope[op * a.sl_cs + a.sl_co + n]) > 0.0f)) val *= kLeak;
-                if (a.add) val += bf2f(a.add[op * a.ad_cs + a.ad_co + n]);
-                if (a.y)
-                    a.y[op * a.y_cs + a.y_co + n] = f2bf(val);
-                else
-                    a.yf[op * a.yf_cs + n] = val;
-            }
-        }
-    }
+    // z-planes per wave: four where that leaves a wave per SIMD, fewer on
+    // smaller grids
+    const int64_t yx = (int64_t)a.batch * ((a.my + 7) / 8) * ((a.mx + 7) / 8);
+    const auto waves = [&](int Z) { return yx * ((a.mz + Z - 1) / Z) * 2 * (a.npad / 32); };
+    const dim3 threads(128 * NC);
+    const auto grid = [&](int Z) { return dim3((unsigned)(yx * ((a.mz + Z - 1) / Z)), (unsigned)(a.npad / (32 * NC)), 1); };
+    if (CC == 16 && waves(4) >= 1024)
+        hipLaunchKernelGGL((conv3_kernel<4, 16, NC>), grid(4), threads, 0, s, a);
+    else if (waves(2) >= 1024)
+        hipLaunchKernelGGL((conv3_kernel<2, CC, NC>), grid(2), threads, 0, s, a);
+    else
+        hipLaunchKernelGGL((conv3_kernel<1, CC, NC>), grid(1), threads, 0, s, a);
 }
 
 // ------------------------------------------------------------------ weight gradient
@@ -739,8 +746,9 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t *x, int32_t 
 
 // ------------------------------------------------------------------ elementwise
 // Weight layouts for the GEMMs from the FP32 master weights W[slot][cin][cout]:
-//   out[ph][n][t][c], with slot = ph (phase layouts) or t (flipped: T-1-t),
-//   value W[slot][c][n] (forward) or W[slot][n][c] (transposed, backward-data).
+//   operands (ph, n, t, c) as weight_operand has them, with slot = ph (phase
+//   layouts) or t (flipped: T-1-t), value W[slot][c][n] (forward) or
+//   W[slot][n][c] (transposed, backward-data).
 struct PrepArgs {
     const float *W;
     int32_t cin, cout, nslots;
@@ -757,13 +765,14 @@ __global__ void prep_weights_kernel(const PrepArgs *jobs)
     const int64_t total = (int64_t)a.nph * a.npad * a.taps * a.crow;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
-        int64_t t = e;
-        const int c = t % a.crow;
-        t /= a.crow;
+        const int lane = (e >> 3) & 63;
+        int64_t t = e >> 9;
+        const int c = 16 * (int)(t % (a.crow / 16)) + 8 * (lane >> 5) + (int)(e & 7);
+        t /= a.crow / 16;
         const int tap = t % a.taps;
         t /= a.taps;
-        const int n = t % a.npad;
-        const int ph = t / a.npad;
+        const int n = 32 * (int)(t % (a.npad / 32)) + (lane & 31);
+        const int ph = t / (a.npad / 32);
         const int slot = a.nph > 1 ? ph : (a.flip ? a.nslots - 1 - tap : tap);
         float v = 0.0f;
         if (a.transposed) {
@@ -1091,25 +1100,17 @@ static hipError_t launch_conv(const ConvArgs &a, hipStream_t s)
     const uint32_t mtot = (uint32_t)a.batch * a.mz * a.my * a.mx;
     const int nt = a.npad % 64 == 0 ? 2 : 1;
     if (a.k == 3 && a.s_in == 1 && a.pad == 1 && a.nph == 1 && a.s_out == 1 && a.cin % 16 == 0) {
-        const unsigned big = (unsigned)a.batch * ((a.mz + kB3 - 1) / kB3) * ((a.my + kB3 - 1) / kB3) *
-                             ((a.mx + kB3 - 1) / kB3);
-        if (big >= 256) {   // enough 8^3 bricks to fill the device
-            // one 32-column tile per wave: with two, the four row tiles'
-            // accumulators and operands need ~275 registers, one wave per
-            // SIMD, and the step was 2.6% slower
-            const dim3 grid(big, a.npad / 32, 1);
-            hipLaunchKernelGGL(conv3_big_kernel<1>, grid, dim3(256), 0, s, a);
-            return hipGetLastError();
+        // Input channels per chunk: 16 on grids of at least 256 bricks of 8^3
+        // (enough workgroups to overlap one's loads with another's products),
+        // 32 on smaller ones (half the barriers).
+        const int64_t bricks = (int64_t)a.batch * ((a.mz + 7) / 8) * ((a.my + 7) / 8) * ((a.mx + 7) / 8);
+        if (bricks >= 256) {
+            if (nt == 2) launch_conv3_as<16, 2>(a, s);
+            else launch_conv3_as<16, 1>(a, s);
+        } else {
+            if (nt == 2) launch_conv3_as<32, 2>(a, s);
+            else launch_conv3_as<32, 1>(a, s);
         }
-        const unsigned bricks = (unsigned)a.batch * ((a.mz + kBZ - 1) / kBZ) * ((a.my + kBY - 1) / kBY) *
-                                ((a.mx + kBX - 1) / kBX);
-        // small grids: 32-column tiles give twice the workgroups
-        const int ntl = (nt == 2 && bricks * (unsigned)(a.npad / 64) < 512) ? 1 : nt;
-        const dim3 grid(bricks, a.npad / (32 * ntl), 1);
-        if (ntl == 2)
-            hipLaunchKernelGGL(conv3_lds_kernel<2>, grid, dim3(256), 0, s, a);
-        else
-            hipLaunchKernelGGL(conv3_lds_kernel<1>, grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
     const dim3 grid((mtot + 127) / 128, a.npad / (32 * nt), a.nph);

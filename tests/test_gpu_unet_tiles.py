@@ -1,0 +1,46 @@
+"""The U-Net's 3^3 convolutions in every form of their dispatch (planes per
+wave, channels per chunk, column tiles), on grids that end inside a brick,
+per element against the FP64 layers on the device's own stored tensors."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_unet import _case, flat, soc  # noqa: F401
+from tests.unet_parity import check_backward_layers, check_forward_layers, print_rows
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("base,n,shape", [
+    (16, 1, (1, 1, 1)),         # one cell
+    (16, 1, (3, 5, 9)),         # one plane per wave, 32 channels per chunk, one column tile
+    (48, 1, (9, 10, 11)),       # a last chunk of 16 channels, two column tiles
+    (16, 1, (40, 47, 37)),      # two planes per wave
+    (64, 1, (31, 30, 26)),      # two planes, two column tiles
+    (16, 1, (2, 128, 121)),     # 16 channels per chunk, one plane
+    (16, 1, (66, 61, 34)),      # four planes, one column tile
+    (64, 1, (50, 51, 33)),      # four planes, two column tiles
+])
+def test_layers_match_oracle(soc, base, n, shape):  # noqa: F811
+    P, x, dy = _case(1, base, n, shape, seed=base)
+    ctx = soc.Context(0)
+    net = soc.UNet(ctx, 2, 2, base, 1, n, shape)
+    net.set_params(flat(P).astype(np.float32))
+    y = net.forward(torch.from_numpy(x.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    rep = check_forward_layers(net, P, n, shape, 2, 2, base, 1, y)
+    rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), n, shape, 2, 2, base, 1)
+    print_rows(rep)
+    ctx.close()
+
+
+@pytest.mark.parametrize("levels,n,shape", [(2, 2, (6, 10, 14)), (3, 1, (12, 20, 28))])
+def test_down_and_up_on_odd_grids(soc, levels, n, shape):  # noqa: F811
+    P, x, dy = _case(levels, 16, n, shape, seed=levels)
+    ctx = soc.Context(0)
+    net = soc.UNet(ctx, 2, 2, 16, levels, n, shape)
+    net.set_params(flat(P).astype(np.float32))
+    y = net.forward(torch.from_numpy(x.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    rep = check_forward_layers(net, P, n, shape, 2, 2, 16, levels, y)
+    rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), n, shape, 2, 2, 16, levels)
+    print_rows(rep)
+    ctx.close()
