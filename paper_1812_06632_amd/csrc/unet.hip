@@ -115,11 +115,12 @@ __device__ inline bf16x8_t weight_operand(const ConvArgs &a, int ph, int ntile, 
 // channels of one row and the tensors are read and written 16 bytes at a time
 // (channels come in multiples of 16); two bytes at a time, the epilogue took
 // as long as the products.  position(row, op): the row's output position;
-// false outside the grid.
+// false outside the grid; asked for rows lane / 4 and lane / 4 + 16, and with
+// kF32 for others where the output is FP32.
 constexpr int kTileRow = 40;   // words per row: rows 4 apart (a write's two halves) on different banks
 constexpr int kTileWords = 32 * kTileRow;
 
-template <typename F>
+template <bool kF32, typename F>
 __device__ __forceinline__ void store_tile(const ConvArgs &a, float *tile, const f32x16_t &acc, int n0, int lane, F position)
 {
     const int half = lane >> 5, r = lane & 31;
@@ -134,7 +135,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, float *tile, const
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (!a.y) {   // FP32 output of a few channels
+    if (kF32 && !a.y) {   // FP32 output of a few channels
         for (int i = lane; i < 32 * a.cout; i += 64) {
             size_t op;
             if (position(i / a.cout, op)) a.yf[op * a.yf_cs + i % a.cout] = tile[(i / a.cout) * kTileRow + i % a.cout];
@@ -167,74 +168,96 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, float *tile, const
     }
 }
 
-template <int NT>
-__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
+// The convolutions between levels: K = 2, stride 2 (down, and the gradient of
+// up), one product over 8 taps; K = 1 with 8 output phases (up, and the
+// gradient of down), 8 products of the same rows.  A wave owns 32 rows (input
+// positions or pairs of them) x NT tiles of 32 columns of `phases`
+// consecutive phases.  A phase is a chain of K^3 cin / 16 steps whose operands
+// come straight from memory, D steps ahead in registers: there is no reuse to
+// stage, and the chain's loads are all there is to wait for on small grids.
+// The ring runs on into the next phase, so its operands arrive during the
+// epilogue.  The input grid is K times the row grid, so all rows read are
+// inside; rows past the end repeat the last and are not stored.
+// Measured, 64^3, base 32, four levels: the three down and three up
+// convolutions of one sample 116 us before (a step's loads waited for, a wave
+// per 32 x 64 tile and phase), 52 now; the six gradients of four samples 250
+// and 180, of which 120 is the level of 64^3, where the tensors' rows of 64
+// bytes are half a cache line.
+template <int NT, int K, int D>
+__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a, int32_t phases)
 {
     __shared__ __attribute__((aligned(16))) float tiles[4][kTileWords];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int half = lane >> 5;
-    const int r = lane & 31;
     const uint32_t mtot = (uint32_t)a.batch * a.mz * a.my * a.mx;
-    const uint32_t tile = (blockIdx.x * 4u + wave) * 32u;
-    const int ph = blockIdx.z;
+    const uint32_t tile = __builtin_amdgcn_readfirstlane((blockIdx.x * (blockDim.x >> 6) + wave) * 32u);
     const int n0 = blockIdx.y * 32 * NT;
     if (tile >= mtot) return;
-
-    // A operand: this lane's row
-    const uint32_t m = tile + r;
-    const bool mval = m < mtot;
-    int b = 0, qz = 0, qy = 0, qx = 0;
-    if (mval) {
-        uint32_t t = m;
+    const auto row_at = [&](uint32_t m, int &qz, int &qy, int &qx) {
+        uint32_t t = min(m, mtot - 1);
         qx = t % a.mx;
         t /= a.mx;
         qy = t % a.my;
         t /= a.my;
         qz = t % a.mz;
-        b = t / a.mz;
+        return (int)(t / a.mz);
+    };
+    int qz, qy, qx;
+    int b = row_at(tile + (lane & 31), qz, qy, qx);
+    const uint16_t *const xrow =
+        a.x + (size_t)(((b * a.iz + K * qz) * a.iy + K * qy) * a.ix + K * qx) * a.x_cs + a.x_co + 8 * half;
+    // output positions (phase 0) of the two rows that this lane stores
+    size_t op0[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        b = row_at(tile + (lane >> 2) + 16 * i, qz, qy, qx);
+        op0[i] = (size_t)((b * a.oz + a.s_out * qz) * a.oy + a.s_out * qy) * a.ox + a.s_out * qx;
     }
-    f32x16_t acc[NT];
-#pragma unroll
-    for (int s = 0; s < NT; ++s)
-        for (int v = 0; v < 16; ++v) acc[s][v] = 0.0f;
 
-    int tap = 0;
-    for (int tz = 0; tz < a.k; ++tz)
-        for (int ty = 0; ty < a.k; ++ty)
-            for (int tx = 0; tx < a.k; ++tx, ++tap) {
-                const int zz = a.s_in * qz + tz - a.pad;
-                const int yy = a.s_in * qy + ty - a.pad;
-                const int xx = a.s_in * qx + tx - a.pad;
-                const bool ok = mval && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && xx >= 0 && xx < a.ix;
-                const uint16_t *xrow =
-                    ok ? a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + 8 * half
-                       : nullptr;
-                for (int c = 0; c < a.cin; c += 16) {
-                    const bf16x8_t A = ok ? ld8(xrow + c) : zero8();
+    const int nc = a.cin / 16, steps = K * K * K * nc;
+    const int ph_end = (blockIdx.z + 1) * phases;
+    // the step that is loaded next: phase, tap, channels
+    int lph = blockIdx.z * phases, tap = 0, c = 0, j = 0;
+    bf16x8_t A[D], B[D][NT];
+    const uint16_t *const wlane = a.w + (size_t)(n0 / 32) * steps * 512 + lane * 8;
+    const size_t wphase = (size_t)(a.npad / 32) * steps * 512, wtile = (size_t)steps * 512;
+    const auto load = [&](int d) {
+        size_t at = c * 16;
+        if (K == 2) at += (size_t)(((tap >> 2) * a.iy + ((tap >> 1) & 1)) * a.ix + (tap & 1)) * a.x_cs;
+        A[d] = ld8(xrow + at);
 #pragma unroll
-                    for (int s = 0; s < NT; ++s) {
-                        const bf16x8_t B = weight_operand(a, ph, n0 / 32 + s, tap, c, lane);
-                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[s], 0, 0, 0);
-                    }
-                }
+        for (int s = 0; s < NT; ++s) B[d][s] = ld8(wlane + lph * wphase + s * wtile + (size_t)j * 512);
+        if (j + 1 < steps) {
+            ++j;
+            if (++c == nc) c = 0, ++tap;
+        } else if (lph + 1 < ph_end) {
+            ++lph, tap = c = j = 0;
+        }   // else: past the end, the last step again
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d);
+    for (int ph = blockIdx.z * phases; ph < ph_end; ++ph) {
+        f32x16_t acc[NT];
+#pragma unroll
+        for (int s = 0; s < NT; ++s)
+            for (int v = 0; v < 16; ++v) acc[s][v] = 0.0f;
+        for (int k = 0; k < steps; k += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+#pragma unroll
+                for (int s = 0; s < NT; ++s)
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[d], B[d][s], acc[s], 0, 0, 0);
+                load(d);
             }
-
-    const int ez = (ph >> 2) & 1, ey = (ph >> 1) & 1, ex = ph & 1;
+        const size_t shift = (size_t)(((ph >> 2) & 1) * a.oy + ((ph >> 1) & 1)) * a.ox + (ph & 1);
 #pragma unroll
-    for (int s = 0; s < NT; ++s)
-        store_tile(a, tiles[wave], acc[s], n0 + 32 * s, lane, [&](int i, size_t &op) {
-            uint32_t t = tile + i;
-            if (t >= mtot) return false;
-            const int px = t % a.mx;
-            t /= a.mx;
-            const int py = t % a.my;
-            t /= a.my;
-            const int pz = t % a.mz;
-            const int pb = t / a.mz;
-            op = (size_t)((pb * a.oz + a.s_out * pz + ez) * a.oy + a.s_out * py + ey) * a.ox + a.s_out * px + ex;
-            return true;
-        });
+        for (int s = 0; s < NT; ++s)
+            store_tile<false>(a, tiles[wave], acc[s], n0 + 32 * s, lane, [&](int row, size_t &op) {
+                op = op0[row >> 4] + shift;
+                return tile + row < mtot;
+            });
+    }
 }
 
 // 3^3 convolutions (stride 1, padding 1) -- most of the network's work --
@@ -408,7 +431,7 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
     float *const tile = reinterpret_cast<float *>(halo) + wave * kTileWords;
 #pragma unroll
     for (int z = 0; z < Z; ++z)
-        store_tile(a, tile, acc[z], n0, lane, [&](int i, size_t &op) {
+        store_tile<true>(a, tile, acc[z], n0, lane, [&](int i, size_t &op) {
             const int pz = z0 + z, py = y0 + (wave & 1) * 4 + (i >> 3), px = x0 + (i & 7);
             op = (size_t)((b * a.oz + pz) * a.oy + py) * a.ox + px;
             return pz < a.mz && py < a.my && px < a.mx;
@@ -1095,9 +1118,31 @@ hipError_t Net::prep_weights(hipStream_t s)
     return hipGetLastError();
 }
 
+template <int K, int D>
+static void launch_between(const ConvArgs &a, hipStream_t s)
+{
+    const uint32_t tiles = ((uint32_t)a.batch * a.mz * a.my * a.mx + 31) / 32, cols = a.npad / 32;
+    // Two column tiles per wave where that leaves a wave per SIMD (rows read
+    // once for both: 39 against 55 us for 131072 rows of 32 -> 64 channels; one
+    // tile with fewer: 7.2 against 8.2 us for 4096 rows of 64 -> 128).
+    const int nt = a.npad % 64 == 0 && (int64_t)tiles * (cols / 2) >= 1024 ? 2 : 1;
+    // Phases one after the other in a wave as long as there are 4 waves per
+    // SIMD: 80 us all 8 in one wave, 95 us one per wave for 131072 rows of
+    // 64 -> 32 channels, where 16 against 15 us for an eighth of the rows.
+    int32_t phases = a.nph;
+    const auto waves = [&] { return (int64_t)tiles * (cols / nt) * (a.nph / phases); };
+    while (phases > 1 && waves() < 4096) phases /= 2;
+    const bool few = waves() < 4096;   // then one wave per workgroup, spread over the chip
+    const int wg = few ? 1 : 4;
+    const dim3 grid((tiles + wg - 1) / wg, cols / nt, a.nph / phases);
+    if (nt == 2)
+        hipLaunchKernelGGL((conv_kernel<2, K, D>), grid, dim3(64 * wg), 0, s, a, phases);
+    else
+        hipLaunchKernelGGL((conv_kernel<1, K, D>), grid, dim3(64 * wg), 0, s, a, phases);
+}
+
 static hipError_t launch_conv(const ConvArgs &a, hipStream_t s)
 {
-    const uint32_t mtot = (uint32_t)a.batch * a.mz * a.my * a.mx;
     const int nt = a.npad % 64 == 0 ? 2 : 1;
     if (a.k == 3 && a.s_in == 1 && a.pad == 1 && a.nph == 1 && a.s_out == 1 && a.cin % 16 == 0) {
         // Input channels per chunk: 16 on grids of at least 256 bricks of 8^3
@@ -1113,11 +1158,12 @@ static hipError_t launch_conv(const ConvArgs &a, hipStream_t s)
         }
         return hipGetLastError();
     }
-    const dim3 grid((mtot + 127) / 128, a.npad / (32 * nt), a.nph);
-    if (nt == 2)
-        hipLaunchKernelGGL(conv_kernel<2>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(conv_kernel<1>, grid, dim3(256), 0, s, a);
+    // Steps ahead D: a divisor of a phase's steps.  K = 2 has 8 per 16
+    // channels; K = 1 reads the deeper level, a multiple of 32 channels.
+    if (a.cin % (a.k == 2 ? 16 : 32) != 0) return hipErrorInvalidValue;
+    if (a.k == 2) launch_between<2, 8>(a, s);
+    else if (a.cin % 64 == 0) launch_between<1, 4>(a, s);
+    else launch_between<1, 2>(a, s);
     return hipGetLastError();
 }
 

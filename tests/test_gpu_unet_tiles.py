@@ -44,3 +44,20 @@ def test_down_and_up_on_odd_grids(soc, levels, n, shape):  # noqa: F811
     rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), n, shape, 2, 2, 16, levels)
     print_rows(rep)
     ctx.close()
+
+
+@pytest.mark.parametrize("base,shape", [
+    (16, (66, 62, 66)),         # up and down: one column tile, two phases per wave
+    (64, (64, 62, 68)),         # two column tiles
+    (48, (10, 6, 14)),          # an odd number of 16 channels, one phase per wave
+])
+def test_between_levels(soc, base, shape):  # noqa: F811
+    P, x, dy = _case(2, base, 1, shape, seed=base)
+    ctx = soc.Context(0)
+    net = soc.UNet(ctx, 2, 2, base, 2, 1, shape)
+    net.set_params(flat(P).astype(np.float32))
+    y = net.forward(torch.from_numpy(x.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    rep = check_forward_layers(net, P, 1, shape, 2, 2, base, 2, y)
+    rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), 1, shape, 2, 2, base, 2)
+    print_rows(rep)
+    ctx.close()
