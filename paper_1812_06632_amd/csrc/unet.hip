@@ -71,6 +71,15 @@ __device__ inline bf16x8_t zero8()
     return __builtin_bit_cast(bf16x8_t, u32x4{0u, 0u, 0u, 0u});
 }
 
+// Workgroup barrier for LDS alone: __syncthreads also waits for every load
+// from memory, among them those made for the next round.
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ------------------------------------------------------------------ conv
 struct ConvArgs {
     const uint16_t *x;
@@ -286,13 +295,15 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a, int32_t phases)
 // Measured, one sample of 64^3, base 32, four levels (122 GFLOP, 0.11 ms at
 // the rate of a large BF16 matrix product): forward 1.21 ms before (each
 // operand read from LDS for one product, weights in rows, two-byte epilogue),
-// 0.43 ms now.  What is left is the latency of a chunk on the small grids (a
+// 0.34 ms now.  What is left is the latency of a chunk on the small grids (a
 // wave per SIMD or less) and, on the large ones, the halo loads between two
 // barriers with two waves per SIMD.
 constexpr int kH3 = 10;                       // halo edge in y and x
 constexpr int kRow3 = kH3 * 16 + 8;           // 168 elements per halo row: an odd number of 16-byte units
 
-template <int Z, int CC, int NC>
+// kFull: the input channels are a multiple of CC (else the last chunk's second
+// half is zero, and its weights are not there to be read).
+template <int Z, int CC, int NC, bool kFull>
 __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_kernel(ConvArgs a)
 {
     constexpr int kThreads = 128 * NC, kHalf = CC / 16;
@@ -332,19 +343,23 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
     const int unit = tid % kUnits, row0 = tid / kUnits;
     const int hx = unit / (CC / 8), hg = unit % (CC / 8);
     const int xx = x0 + hx - 1;
-    const bool in_x = row0 < kRowsAt && xx >= 0 && xx < a.ix;
     uint16_t *const hdst = halo + (hg >> 1) * kPlane + row0 * kRow3 + hx * 16 + 8 * (hg & 1);
+    // Loads are unconditional, from the nearest position inside the volume,
+    // and zeroed when stored: with branches around them the compiler cannot
+    // count them and waits for every load in flight, the next weights too
+    // (178 -> 171 us for four samples of 64^3 and 32 -> 64 channels).
     const auto load_row = [&](int first, int e, int c0) {
         const int row = first + kRowsAt * e;
-        const int zz = z0 + row / kH3 - 1, yy = y0 + row % kH3 - 1;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (in_x && row < kRows && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && c0 + 8 * hg < a.cin)
-            v = *reinterpret_cast<const u32x4 *>(
-                a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + c0 + 8 * hg);
-        return v;
+        const int zz = min(max(z0 + row / kH3 - 1, 0), a.iz - 1), yy = min(max(y0 + row % kH3 - 1, 0), a.iy - 1);
+        const int xc = min(max(xx, 0), a.ix - 1), c = min(c0 + 8 * hg, a.cin - 8);
+        return *reinterpret_cast<const u32x4 *>(a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xc) * a.x_cs + a.x_co + c);
     };
-    const auto store_row = [&](int e, u32x4 v) {
-        if (row0 < kRowsAt && row0 + kRowsAt * e < kRows) *reinterpret_cast<u32x4 *>(hdst + kRowsAt * e * kRow3) = v;
+    const auto store_row = [&](int first, int e, int c0, u32x4 v) {
+        const int row = first + kRowsAt * e;
+        const int zz = z0 + row / kH3 - 1, yy = y0 + row % kH3 - 1;
+        const bool in = xx >= 0 && xx < a.ix && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && c0 + 8 * hg < a.cin;
+        if (row0 < kRowsAt && row < kRows)
+            *reinterpret_cast<u32x4 *>(hdst + kRowsAt * e * kRow3) = in ? v : u32x4{0u, 0u, 0u, 0u};
     };
     u32x4 ph[kAhead ? kPer : 1];
     const auto load_halo = [&](int c0) {
@@ -352,15 +367,21 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
         for (int e = 0; e < kPer; ++e) ph[e] = load_row(row0, e, c0);
     };
 
+    // (the loads come in the order of the loop's, halo before weights: what a
+    // wait may leave in flight is the least over the ways that lead to it)
+    if (kAhead) load_halo(0);
+    __builtin_amdgcn_sched_barrier(0);
     f32x16_t acc[Z];
 #pragma unroll
     for (int z = 0; z < Z; ++z)
         for (int v = 0; v < 16; ++v) acc[z][v] = 0.0f;
     bf16x8_t B[27][kHalf];
 #pragma unroll
-    for (int t = 0; t < 27; ++t)
+    for (int t = 0; t < 27; ++t) {
 #pragma unroll
-        for (int h = 0; h < kHalf; ++h) B[t][h] = h == 0 || a.cin > 16 ? weights(t, 16 * h) : zero8();
+        for (int h = 0; h < kHalf; ++h) B[t][h] = kFull || h == 0 || a.cin > 16 ? weights(t, 16 * h) : zero8();
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     // products of one chunk; kNext: another one follows, its weights are loaded
     const auto chunk = [&](auto has_next, int c0) {
@@ -392,17 +413,16 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
                 if (kNext && z == Z - 1)
 #pragma unroll
                     for (int h = 0; h < kHalf; ++h)
-                        B[9 * tz + t][h] = h == 0 || cn + 16 < a.cin ? weights(9 * tz + t, cn + 16 * h) : zero8();
+                        B[9 * tz + t][h] = kFull || h == 0 || cn + 16 < a.cin ? weights(9 * tz + t, cn + 16 * h) : zero8();
             }
             __builtin_amdgcn_sched_barrier(0);   // or the scheduler reads all operands at once and spills
         }
     };
-    if (kAhead) load_halo(0);
     for (int c0 = 0; c0 < a.cin; c0 += CC) {
-        __syncthreads();   // the previous chunk has been consumed
+        lds_barrier();   // the previous chunk has been consumed
         if (kAhead) {
 #pragma unroll
-            for (int e = 0; e < kPer; ++e) store_row(e, ph[e]);
+            for (int e = 0; e < kPer; ++e) store_row(row0, e, c0, ph[e]);
         } else {
             constexpr int kBatch = 5;   // rows in flight per lane
             int first = row0;           // as if new in every chunk: addresses kept from chunk to chunk would spill
@@ -414,20 +434,21 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
 #pragma unroll
                 for (int e = 0; e < kBatch; ++e) v[e] = load_row(first, e0 + e, c0);
 #pragma unroll
-                for (int e = 0; e < kBatch; ++e) store_row(e0 + e, v[e]);
+                for (int e = 0; e < kBatch; ++e) store_row(first, e0 + e, c0, v[e]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (c0 + CC < a.cin) {
             if (kAhead) load_halo(c0 + CC);
+            __builtin_amdgcn_sched_barrier(0);
             chunk(std::true_type{}, c0);
         } else {
             chunk(std::false_type{}, c0);
         }
     }
 
-    __syncthreads();   // the halo has been consumed: its LDS holds the tiles
+    lds_barrier();   // the halo has been consumed: its LDS holds the tiles
     float *const tile = reinterpret_cast<float *>(halo) + wave * kTileWords;
 #pragma unroll
     for (int z = 0; z < Z; ++z)
@@ -438,7 +459,7 @@ __global__ __launch_bounds__(128 * NC, Z >= 4 && CC == 16 ? 2 : 1) void conv3_ke
         });
 }
 
-template <int CC, int NC>
+template <int CC, int NC, bool kFull>
 static void launch_conv3_as(const ConvArgs &a, hipStream_t s)
 {
     // z-planes per wave: four where that leaves a wave per SIMD, fewer on
@@ -448,11 +469,11 @@ static void launch_conv3_as(const ConvArgs &a, hipStream_t s)
     const dim3 threads(128 * NC);
     const auto grid = [&](int Z) { return dim3((unsigned)(yx * ((a.mz + Z - 1) / Z)), (unsigned)(a.npad / (32 * NC)), 1); };
     if (CC == 16 && waves(4) >= 1024)
-        hipLaunchKernelGGL((conv3_kernel<4, 16, NC>), grid(4), threads, 0, s, a);
+        hipLaunchKernelGGL((conv3_kernel<4, 16, NC, true>), grid(4), threads, 0, s, a);
     else if (waves(2) >= 1024)
-        hipLaunchKernelGGL((conv3_kernel<2, CC, NC>), grid(2), threads, 0, s, a);
+        hipLaunchKernelGGL((conv3_kernel<2, CC, NC, kFull>), grid(2), threads, 0, s, a);
     else
-        hipLaunchKernelGGL((conv3_kernel<1, CC, NC>), grid(1), threads, 0, s, a);
+        hipLaunchKernelGGL((conv3_kernel<1, CC, NC, kFull>), grid(1), threads, 0, s, a);
 }
 
 // ------------------------------------------------------------------ weight gradient
@@ -524,7 +545,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
             *reinterpret_cast<u32x4 *>(&xs[wave][rr][cg]) = vx;
             *reinterpret_cast<u32x4 *>(&ds[wave][rr][cg]) = vd;
         }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int kk = 0; kk < kWgStep / 16; ++kk) {
             u32x4 pa, pb;
@@ -536,12 +557,12 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pa),
                                                           __builtin_bit_cast(bf16x8_t, pb), acc, 0, 0, 0);
         }
-        __syncthreads();
+        lds_barrier();
     }
     // reduce the four waves' tiles in a fixed order
     if (wave > 0)
         for (int v = 0; v < 16; ++v) red[wave - 1][lane][v] = acc[v];
-    __syncthreads();
+    lds_barrier();
     if (wave == 0) {
         for (int w = 0; w < 3; ++w)
             for (int v = 0; v < 16; ++v) acc[v] += red[w][lane][v];
@@ -643,7 +664,7 @@ __global__ __launch_bounds__(192, 2) void wgrad3_kernel(WgradArgs a)
     if (b_begin < b_end) load_halo(brick(b_begin));
     for (uint32_t bi = b_begin; bi < b_end; ++bi) {
         const Brick k = brick(bi);
-        __syncthreads();   // previous brick consumed
+        lds_barrier();   // previous brick consumed
         for (int e = tid; e < kDyItems; e += 192) {
             const int pos = e >> 2, g = e & 3;
             const int lx = pos & 7, ly = (pos >> 3) & 7, lz = pos >> 6;
@@ -661,7 +682,7 @@ __global__ __launch_bounds__(192, 2) void wgrad3_kernel(WgradArgs a)
             const int hx = pos % 10, hy = (pos / 10) % kGHY, hz = pos / (10 * kGHY);
             if (e < kHaloItems) *reinterpret_cast<u32x4 *>(&xL[((hz * kGHY + hy) * kGHX + hx) * 32 + 8 * (e & 3)]) = ph[j];
         }
-        __syncthreads();
+        lds_barrier();
         if (bi + 1 < b_end) load_halo(brick(bi + 1));
         if (want_bias)
             for (int pos = tid >> 5; pos < kGZ * kGY * kGX; pos += 6) bsum += bf2f(dL[pos * 32 + (tid & 31)]);
@@ -692,7 +713,7 @@ __global__ __launch_bounds__(192, 2) void wgrad3_kernel(WgradArgs a)
     if (want_bias) {
         __shared__ float bred[6][32];
         bred[tid >> 5][tid & 31] = bsum;
-        __syncthreads();
+        lds_barrier();
         if (tid < 32 && o0 + tid < a.cout) {
             float t = 0.0f;
             for (int q = 0; q < 6; ++q) t += bred[q][tid];
@@ -1143,18 +1164,25 @@ static void launch_between(const ConvArgs &a, hipStream_t s)
 
 static hipError_t launch_conv(const ConvArgs &a, hipStream_t s)
 {
-    const int nt = a.npad % 64 == 0 ? 2 : 1;
     if (a.k == 3 && a.s_in == 1 && a.pad == 1 && a.nph == 1 && a.s_out == 1 && a.cin % 16 == 0) {
         // Input channels per chunk: 16 on grids of at least 256 bricks of 8^3
         // (enough workgroups to overlap one's loads with another's products),
         // 32 on smaller ones (half the barriers).
-        const int64_t bricks = (int64_t)a.batch * ((a.mz + 7) / 8) * ((a.my + 7) / 8) * ((a.mx + 7) / 8);
-        if (bricks >= 256) {
-            if (nt == 2) launch_conv3_as<16, 2>(a, s);
-            else launch_conv3_as<16, 1>(a, s);
+        const int64_t yx = (int64_t)a.batch * ((a.my + 7) / 8) * ((a.mx + 7) / 8);
+        const bool large = yx * ((a.mz + 7) / 8) >= 256;
+        // Column tiles per workgroup: two share a halo, one where two would
+        // leave CUs without a workgroup (its weights then come over two CUs'
+        // memory paths: 12.4 against 13.6 us for 16^3 and 128 -> 128 channels).
+        const bool two = a.npad % 64 == 0 && (large || yx * a.mz * (a.npad / 64) >= 256);
+        if (large) {
+            if (two) launch_conv3_as<16, 2, true>(a, s);
+            else launch_conv3_as<16, 1, true>(a, s);
+        } else if (a.cin % 32 == 0) {
+            if (two) launch_conv3_as<32, 2, true>(a, s);
+            else launch_conv3_as<32, 1, true>(a, s);
         } else {
-            if (nt == 2) launch_conv3_as<32, 2>(a, s);
-            else launch_conv3_as<32, 1>(a, s);
+            if (two) launch_conv3_as<32, 2, false>(a, s);
+            else launch_conv3_as<32, 1, false>(a, s);
         }
         return hipGetLastError();
     }

@@ -17,6 +17,9 @@ torch = pytest.importorskip("torch")
     (48, 1, (9, 10, 11)),       # a last chunk of 16 channels, two column tiles
     (16, 1, (40, 47, 37)),      # two planes per wave
     (64, 1, (31, 30, 26)),      # two planes, two column tiles
+    (64, 1, (18, 26, 27)),      # one plane, two column tiles
+    (80, 1, (20, 26, 27)),      # the same, a last chunk of 16 channels
+    (64, 1, (5, 9, 10)),        # 64 columns, one column tile
     (16, 1, (2, 128, 121)),     # 16 channels per chunk, one plane
     (16, 1, (66, 61, 34)),      # four planes, one column tile
     (64, 1, (50, 51, 33)),      # four planes, two column tiles
