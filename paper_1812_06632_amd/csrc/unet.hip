@@ -586,150 +586,280 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
 // (ds_read_b64_tr_b16) delivers from the channels-last tiles: within each
 // group of 16 lanes, lane s gives the address of 4 channels (4 (s mod 4)
 // onwards) at position s / 4, and lane i receives channel i at the 4
-// positions.  Wave w takes the taps with tz = w; a tap's x-shift is an
-// offset of the positions read.
+// positions.
+//
+// Three such reads hold the 10 positions of an input row, and the operands
+// of its three x-taps are made from them in registers (the middle one by
+// 16-bit shifts); the row of y-tap 2 is y-tap 0's of the next K-step.  The
+// 27 taps are split over four waves, one per SIMD: wave w < 3 takes z-tap w's
+// first 7 in (y, x) order, wave 3 the last two x-taps of y-tap 2 of every
+// z-tap (6).  A chunk's bricks go up in z, so that two of a brick's four halo
+// planes are the last one's and stay in LDS.  The next brick's loads are made
+// during the products, from the nearest position inside the volume and zeroed
+// when stored (see conv3_kernel).
+//
+// Measured, 4 x 64^3 positions, 32 x 32 channels (58 GFLOP, 52 us at the rate
+// of a large BF16 matrix product): 110 us before (three waves of 9 taps, two
+// reads per operand, bricks along x with whole halos, dy loaded when staged),
+// 67 now; the 16 layers of a gradient of base 32, four levels 1090 and 740.
+// Without the products it is 39, of which the partial sums' stores (56 MB)
+// take a third.
 constexpr int kGZ = 2, kGY = 8, kGX = 8;                 // brick
-constexpr int kGHZ = kGZ + 2, kGHY = kGY + 2, kGHX = 16;  // halo (x padded to 16)
+constexpr int kGHZ = kGZ + 2, kGHY = kGY + 2, kGHX = 12;  // halo (x padded from 10 to three reads)
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// 4 positions (pos0 .. pos0 + 3, row stride 32 channels) of the lane's
-// channel c0 + (lane mod 16), read transposed from a channels-last tile.
-__device__ inline uint2 tr_read4(const uint16_t *tile, int pos0, int c0, int lane)
+// 4 positions (of row stride 32 channels) of the lane's channel, read
+// transposed from a channels-last tile; p: see tr_lane.
+__device__ inline uint2 tr_read4(const uint16_t *p)
 {
-    const int s = lane & 15;
-    const uint16_t *p = tile + (pos0 + (s >> 2)) * 32 + c0 + 4 * (s & 3);
     const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
     return __builtin_bit_cast(uint2, v);
 }
 
-__global__ __launch_bounds__(192, 2) void wgrad3_kernel(WgradArgs a)
+// The lane's share of a transpose read's address.
+__device__ inline int tr_lane(int lane)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t xL[kGHZ * kGHY * kGHX * 32];   // 40 KB, [hz][hy][hx][ch]
-    __shared__ __attribute__((aligned(16))) uint16_t dL[kGZ * kGY * kGX * 32];      // 8 KB, [lz][ly][lx][ch]
+    return ((lane & 15) >> 2) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+}
+
+// An input row: 10 positions of the lane's channel, and its x-taps.
+struct TapRow { u32x4 v; uint32_t last; };
+
+__device__ inline TapRow tap_row(const uint16_t *p)
+{
+    const uint2 r0 = tr_read4(p), r1 = tr_read4(p + 4 * 32);
+    return {u32x4{r0.x, r0.y, r1.x, r1.y}, tr_read4(p + 8 * 32).x};
+}
+
+template <int TX>
+__device__ inline bf16x8_t tap_operand(const TapRow &t)
+{
+    const auto mid = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_alignbit(hi, lo, 16); };
+    u32x4 v = t.v;
+    if (TX == 1) v = u32x4{mid(v[1], v[0]), mid(v[2], v[1]), mid(v[3], v[2]), mid(t.last, v[3])};
+    if (TX == 2) v = u32x4{v[1], v[2], v[3], t.last};
+    return __builtin_bit_cast(bf16x8_t, v);
+}
+
+__global__ __launch_bounds__(256, 2) void wgrad3_kernel(WgradArgs a)
+{
+    constexpr int kThreads = 256, kXWords = kGHZ * kGHY * kGHX * 32;
+    __shared__ __attribute__((aligned(16))) uint16_t xL[kXWords];                // 30 KB, [hz][hy][hx][ch]
+    __shared__ __attribute__((aligned(16))) uint16_t dL[kGZ * kGY * kGX * 32];   // 8 KB, [lz][ly][lx][ch]
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int tz = tid >> 6;   // wave = z-tap
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5;
     const int r = lane & 31;
-    const int cg = 16 * ((lane >> 4) & 1);   // channel group of the lane's 16-lane group
     const int ntile_o = (a.cout + 31) / 32;
     const int i0 = (blockIdx.y / ntile_o) * 32;
     const int o0 = (blockIdx.y % ntile_o) * 32;
     const int nbx = (a.mx + kGX - 1) / kGX, nby = (a.my + kGY - 1) / kGY, nbz = (a.mz + kGZ - 1) / kGZ;
     const uint32_t nb = (uint32_t)a.batch * nbz * nby * nbx;
-    const uint32_t b_begin = blockIdx.x * a.chunk, b_end = min(b_begin + a.chunk, nb);
+    // neighbouring columns share halos: consecutive chunks on one XCD
+    uint32_t chunk = blockIdx.x;
+    if (gridDim.x % 8 == 0) chunk = (chunk % 8) * (gridDim.x / 8) + chunk / 8;
+    const uint32_t b_begin = chunk * a.chunk, b_end = min(b_begin + a.chunk, nb);
 
     // workgroups of the first input-channel tile also sum dy per output
-    // channel (the bias gradient): thread (o = tid % 32, part = tid / 32)
-    // adds the staged positions part, part + 6, ...
+    // channel (the bias gradient): a thread adds the 8 channels of the
+    // positions that it stages
     const bool want_bias = i0 == 0;
-    float bsum = 0.0f;
+    float bsum[8];
+    for (int j = 0; j < 8; ++j) bsum[j] = 0.0f;
 
-    f32x16_t acc[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q)
-        for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
-
-    // The next brick's input halo (the larger tile) is loaded into registers
-    // while the current brick is multiplied: 9 16-byte loads per thread
-    // (1600 items over 192 threads); the dy tile is loaded when staged.
-    constexpr int kDyItems = kGZ * kGY * kGX * 4, kHaloItems = kGHZ * kGHY * 10 * 4;
-    constexpr int kHaloPer = (kHaloItems + 191) / 192;
-    u32x4 ph[kHaloPer];
-    struct Brick { int b, z0, y0, x0; };
-    auto brick = [&](uint32_t bi) {
-        uint32_t t = bi;
-        const int bxi = t % nbx;
+    // 16-byte items: two halo planes or a dy tile; thread t's are t, t + 256,
+    // ...: all of one channel group g
+    constexpr int kDyPer = kGZ * kGY * kGX * 4 / kThreads, kHaloItems = 2 * kGHY * 10 * 4;
+    constexpr int kHaloPer = (kHaloItems + kThreads - 1) / kThreads;
+    const int g = tid & 3;
+    const bool x_in = i0 + 8 * g < a.x_c, d_in = o0 + 8 * g < a.dy_c;
+    const uint16_t *const xg = a.x + a.x_co + (x_in ? i0 + 8 * g : 0);
+    const uint16_t *const dg = a.dy + a.dy_co + (d_in ? o0 + 8 * g : 0);
+    u32x4 ph[kHaloPer], pd[kDyPer];
+    uint32_t h_in = 0, dy_in = 0;   // items inside the volume
+    struct Brick { int b, bz, y0, x0; };
+    const auto brick = [&](uint32_t t) {
+        const int bz = t % nbz;
+        t /= nbz;
+        const int x0 = (int)(t % nbx) * kGX;
         t /= nbx;
-        const int byi = t % nby;
-        t /= nby;
-        const int bzi = t % nbz;
-        return Brick{(int)(t / nbz), bzi * kGZ, byi * kGY, bxi * kGX};
+        return Brick{(int)(t / nby), bz, (int)(t % nby) * kGY, x0};
     };
-    auto load_halo = [&](const Brick &k) {
+    const auto load_planes = [&](const Brick &k, int pair) {
+        h_in = 0;
 #pragma unroll
         for (int j = 0; j < kHaloPer; ++j) {
-            const int e = tid + 192 * j;
-            ph[j] = u32x4{0u, 0u, 0u, 0u};
-            const int pos = e >> 2, g = e & 3;
-            const int hx = pos % 10, hy = (pos / 10) % kGHY, hz = pos / (10 * kGHY);
-            const int zz = k.z0 + hz - 1, yy = k.y0 + hy - 1, xx = k.x0 + hx - 1;
-            if (e < kHaloItems && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && xx >= 0 && xx < a.ix &&
-                i0 + 8 * g < a.x_c)
-                ph[j] = *reinterpret_cast<const u32x4 *>(
-                    a.x + (size_t)(((k.b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + i0 + 8 * g);
+            const int pos = (tid + kThreads * j) >> 2, row = pos / 10;
+            const int zz = k.bz * kGZ + 2 * pair + row / kGHY - 1, yy = k.y0 + row % kGHY - 1, xx = k.x0 + pos % 10 - 1;
+            h_in |= (uint32_t)(x_in & ((uint32_t)zz < (uint32_t)a.iz) & ((uint32_t)yy < (uint32_t)a.iy) & ((uint32_t)xx < (uint32_t)a.ix)) << j;
+            const int zc = min(max(zz, 0), a.iz - 1), yc = min(max(yy, 0), a.iy - 1), xc = min(max(xx, 0), a.ix - 1);
+            ph[j] = *reinterpret_cast<const u32x4 *>(xg + (size_t)(((k.b * a.iz + zc) * a.iy + yc) * a.ix + xc) * a.x_cs);
         }
     };
-    if (b_begin < b_end) load_halo(brick(b_begin));
-    for (uint32_t bi = b_begin; bi < b_end; ++bi) {
-        const Brick k = brick(bi);
-        lds_barrier();   // previous brick consumed
-        for (int e = tid; e < kDyItems; e += 192) {
-            const int pos = e >> 2, g = e & 3;
-            const int lx = pos & 7, ly = (pos >> 3) & 7, lz = pos >> 6;
-            const int zz = k.z0 + lz, yy = k.y0 + ly, xx = k.x0 + lx;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (zz < a.mz && yy < a.my && xx < a.mx && o0 + 8 * g < a.dy_c)
-                v = *reinterpret_cast<const u32x4 *>(
-                    a.dy + (size_t)(((k.b * a.oz + zz) * a.oy + yy) * a.ox + xx) * a.dy_cs + a.dy_co + o0 + 8 * g);
-            *reinterpret_cast<u32x4 *>(&dL[pos * 32 + 8 * g]) = v;
+    const auto load_dy = [&](const Brick &k) {
+        dy_in = 0;
+#pragma unroll
+        for (int j = 0; j < kDyPer; ++j) {
+            const int pos = (tid + kThreads * j) >> 2;
+            const int zz = k.bz * kGZ + (pos >> 6), yy = k.y0 + ((pos >> 3) & 7), xx = k.x0 + (pos & 7);
+            dy_in |= (uint32_t)(d_in & (zz < a.mz) & (yy < a.my) & (xx < a.mx)) << j;
+            pd[j] = *reinterpret_cast<const u32x4 *>(
+                dg + (size_t)(((k.b * a.oz + min(zz, a.oz - 1)) * a.oy + min(yy, a.oy - 1)) * a.ox + min(xx, a.ox - 1)) * a.dy_cs);
         }
+    };
+    constexpr int kPlane = kGHY * kGHX * 32;
+    // halo planes 0, 1 (pair 0) and 2, 3 of brick bz: a pair keeps its place
+    // when it becomes the next brick's first
+    const auto place = [&](int bz, int plane) { return (((plane >> 1) ^ bz) & 1) * 2 + (plane & 1); };
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const auto store_planes = [&](int bz, int pair) {
+        uint16_t *const to = xL + place(bz, 2 * pair) * kPlane + 8 * g;
 #pragma unroll
         for (int j = 0; j < kHaloPer; ++j) {
-            const int e = tid + 192 * j;
-            const int pos = e >> 2;
-            const int hx = pos % 10, hy = (pos / 10) % kGHY, hz = pos / (10 * kGHY);
-            if (e < kHaloItems) *reinterpret_cast<u32x4 *>(&xL[((hz * kGHY + hy) * kGHX + hx) * 32 + 8 * (e & 3)]) = ph[j];
+            const int e = tid + kThreads * j, pos = e >> 2;
+            if (e < kHaloItems)
+                *reinterpret_cast<u32x4 *>(to + ((pos / 10) * kGHX + pos % 10) * 32) = (h_in >> j) & 1 ? ph[j] : zero;
         }
-        lds_barrier();
-        if (bi + 1 < b_end) load_halo(brick(bi + 1));
-        if (want_bias)
-            for (int pos = tid >> 5; pos < kGZ * kGY * kGX; pos += 6) bsum += bf2f(dL[pos * 32 + (tid & 31)]);
-        // (the row loop stays rolled: unrolled, the hoisted transpose reads
-        // need 336 registers, one wave per SIMD; rolled, 188)
-#pragma unroll
-        for (int lz = 0; lz < kGZ; ++lz)
-#pragma unroll 1
-            for (int m = 0; m < kGY / 2; ++m) {
-                const int ly = 2 * m + half;   // this lane's x-row of the K-step
-                const int drow = (lz * kGY + ly) * kGX;
-                const uint2 b0 = tr_read4(dL, drow, cg, lane), b1 = tr_read4(dL, drow + 4, cg, lane);
-                const bf16x8_t B = __builtin_bit_cast(bf16x8_t, u32x4{b0.x, b0.y, b1.x, b1.y});
-#pragma unroll
-                for (int ty = 0; ty < 3; ++ty) {
-                    const int xrow = ((lz + tz) * kGHY + ly + ty) * kGHX;
-#pragma unroll
-                    for (int tx = 0; tx < 3; ++tx) {
-                        const uint2 a0 = tr_read4(xL, xrow + tx, cg, lane), a1 = tr_read4(xL, xrow + tx + 4, cg, lane);
-                        const bf16x8_t A = __builtin_bit_cast(bf16x8_t, u32x4{a0.x, a0.y, a1.x, a1.y});
-                        acc[3 * ty + tx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[3 * ty + tx], 0, 0, 0);
-                    }
-                }
+    };
+
+    // the products of one brick; xz: the planes of z-taps
+    const int x_lane = tr_lane(lane) + half * kGHX * 32;
+    const uint16_t *const dw = dL + tr_lane(lane) + half * kGX * 32;
+    constexpr int kSteps = kGZ * kGY / 2;
+    const auto x_at = [&](const uint16_t *plane, int i, int ty) {   // K-step i
+        return tap_row(plane + (2 * (i % (kGY / 2)) + ty) * kGHX * 32);
+    };
+    const auto dy_at = [&](int i) {
+        const uint16_t *const p = dw + i * 2 * kGX * 32;
+        const uint2 b0 = tr_read4(p), b1 = tr_read4(p + 4 * 32);
+        return __builtin_bit_cast(bf16x8_t, u32x4{b0.x, b0.y, b1.x, b1.y});
+    };
+    const auto mma = [](bf16x8_t A, bf16x8_t B, f32x16_t c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, c, 0, 0, 0); };
+    // Rows are read one ahead; the scheduling barriers keep the reads before
+    // the products that hide them, and further ones from being hoisted.
+    const auto stage = [&](auto products) {
+        load_planes(brick(b_begin), 0);
+        for (uint32_t bi = b_begin; bi < b_end; ++bi) {
+            const Brick k = brick(bi), n = brick(min(bi + 1, b_end - 1));
+            lds_barrier();   // the previous brick has been consumed
+            if (bi == b_begin || k.bz == 0) {   // a column's first: nothing is there yet
+                if (bi != b_begin) load_planes(k, 0);
+                store_planes(k.bz, 0);
+                load_planes(k, 1);
+                load_dy(k);
             }
+            store_planes(k.bz, 1);
+#pragma unroll
+            for (int j = 0; j < kDyPer; ++j) {
+                const u32x4 v = (dy_in >> j) & 1 ? pd[j] : zero;
+                *reinterpret_cast<u32x4 *>(&dL[((tid + kThreads * j) >> 2) * 32 + 8 * g]) = v;
+                if (want_bias)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        bsum[2 * w] += bf2f((uint16_t)(v[w] & 0xffffu));
+                        bsum[2 * w + 1] += bf2f((uint16_t)(v[w] >> 16));
+                    }
+            }
+            lds_barrier();
+            load_planes(n, 1);
+            load_dy(n);
+            __builtin_amdgcn_sched_barrier(0);
+            products(k.bz);
+        }
+    };
+    float *out = a.part + (size_t)chunk * ((size_t)27 * a.cin * a.cout + a.cout);
+    const auto store = [&](const f32x16_t &acc, int tap) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {   // rows = input channels, columns = output channels
+            const int i = i0 + 8 * (v >> 2) + 4 * half + (v & 3);
+            const int o = o0 + r;
+            if (i < a.cin && o < a.cout) out[((size_t)tap * a.cin + i) * a.cout + o] = acc[v];
+        }
+    };
+    // (each kind of wave has the whole loop, with as many barriers, to itself:
+    // with one loop around both, each kept accumulators of its own)
+    if (wave < 3) {
+        f32x16_t acc[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+            for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
+        stage([&](int bz) {
+            const uint16_t *const xz[2] = {xL + x_lane + place(bz, wave) * kPlane, xL + x_lane + place(bz, wave + 1) * kPlane};
+            TapRow t = x_at(xz[0], 0, 0), n;
+            bf16x8_t B = dy_at(0);
+#pragma unroll
+            for (int i = 0; i < kSteps; ++i) {
+                n = x_at(xz[i / (kGY / 2)], i, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[0] = mma(tap_operand<0>(t), B, acc[0]);
+                acc[1] = mma(tap_operand<1>(t), B, acc[1]);
+                acc[2] = mma(tap_operand<2>(t), B, acc[2]);
+                __builtin_amdgcn_sched_barrier(0);
+                t = x_at(xz[i / (kGY / 2)], i, 2);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[3] = mma(tap_operand<0>(n), B, acc[3]);
+                acc[4] = mma(tap_operand<1>(n), B, acc[4]);
+                acc[5] = mma(tap_operand<2>(n), B, acc[5]);
+                __builtin_amdgcn_sched_barrier(0);
+                const int k = min(i + 1, kSteps - 1);
+                const bool plane = k % (kGY / 2) == 0;   // a new z-plane: no row in common
+                if (plane) n = x_at(xz[k / (kGY / 2)], k, 0);
+                const bf16x8_t next = dy_at(k);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[6] = mma(tap_operand<0>(t), B, acc[6]);
+                if (plane) t = n;
+                B = next;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+#pragma unroll
+        for (int q = 0; q < 7; ++q) store(acc[q], 9 * wave + q);
+    } else {
+        f32x16_t acc[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
+        stage([&](int bz) {
+            const uint16_t *xz[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) xz[p] = xL + x_lane + place(bz, p) * kPlane;
+            TapRow t = x_at(xz[0], 0, 2), n;
+            bf16x8_t B = dy_at(0);
+#pragma unroll
+            for (int i = 0; i < kSteps; ++i) {
+                const int k = min(i + 1, kSteps - 1);
+                bf16x8_t next = B;
+#pragma unroll
+                for (int tz = 0; tz < 3; ++tz) {
+                    n = tz < 2 ? x_at(xz[i / (kGY / 2) + tz + 1], i, 2) : x_at(xz[k / (kGY / 2)], k, 2);
+                    if (tz == 2) next = dy_at(k);
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[2 * tz] = mma(tap_operand<1>(t), B, acc[2 * tz]);
+                    acc[2 * tz + 1] = mma(tap_operand<2>(t), B, acc[2 * tz + 1]);
+                    t = n;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                B = next;
+            }
+        });
+#pragma unroll
+        for (int q = 0; q < 6; ++q) store(acc[q], 9 * (q >> 1) + 7 + (q & 1));
     }
-    // bias partials of this chunk, after all weight partials: the six parts
-    // of each output channel added in order
+    // bias partials of this chunk, after all weight partials: the 64 threads
+    // of each channel group added in order
     if (want_bias) {
-        __shared__ float bred[6][32];
-        bred[tid >> 5][tid & 31] = bsum;
+        float *const bred = reinterpret_cast<float *>(xL);   // [8][256]
+        lds_barrier();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) bred[j * kThreads + tid] = bsum[j];
         lds_barrier();
         if (tid < 32 && o0 + tid < a.cout) {
             float t = 0.0f;
-            for (int q = 0; q < 6; ++q) t += bred[q][tid];
+            for (int q = 0; q < kThreads / 4; ++q) t += bred[(tid & 7) * kThreads + 4 * q + (tid >> 3)];
             const size_t row = (size_t)27 * a.cin * a.cout + a.cout;   // a chunk's weight partials, then its bias partials
-            a.part[(size_t)blockIdx.x * row + (size_t)27 * a.cin * a.cout + o0 + tid] = t;
-        }
-    }
-    // partials of this chunk: rows = input channels, columns = output channels
-    float *out = a.part + (size_t)blockIdx.x * ((size_t)27 * a.cin * a.cout + a.cout);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        const int tap = tz * 9 + q;
-        for (int v = 0; v < 16; ++v) {
-            const int i = i0 + 8 * (v >> 2) + 4 * half + (v & 3);
-            const int o = o0 + r;
-            if (i < a.cin && o < a.cout) out[((size_t)tap * a.cin + i) * a.cout + o] = acc[q][v];
+            a.part[(size_t)chunk * row + (size_t)27 * a.cin * a.cout + o0 + tid] = t;
         }
     }
 }
@@ -942,7 +1072,8 @@ Net::WgradPlan Net::plan_wgrad(const Layer &L, int32_t n) const
         const int64_t nb = (int64_t)n * (((nz_ >> l) + kGZ - 1) / kGZ) * (((ny_ >> l) + kGY - 1) / kGY) *
                            (((nx_ >> l) + kGX - 1) / kGX);
         // about 512 workgroups in all: two per CU resident at once, one round
-        // (measured 4 x 64^3 step: 6.05 ms; 384: 6.22, 768: 6.59, 1024: 6.62)
+        // (measured 4 x 64^3, base 32, four levels, with the sums of the
+        // partials: 1.13 ms; 256: 1.19, 384: 1.23, 768: 1.41, 1024: 1.50)
         int64_t chunks = std::min<int64_t>(nb, std::max<int64_t>(1, 512 / ctiles));
         p.chunk = (uint32_t)((nb + chunks - 1) / chunks);
         p.chunks = (nb + p.chunk - 1) / p.chunk;
@@ -1318,7 +1449,7 @@ hipError_t Net::conv_wgrad(const Layer &L, int32_t n, const View &x, const View 
     a.part = d_part_;
     const unsigned ctiles = (unsigned)(((L.cin + 31) / 32) * ((L.cout + 31) / 32));
     if (p.bricks)
-        hipLaunchKernelGGL(wgrad3_kernel, dim3((unsigned)p.chunks, ctiles, 1), dim3(192), 0, s, a);
+        hipLaunchKernelGGL(wgrad3_kernel, dim3((unsigned)p.chunks, ctiles, 1), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL(wgrad_kernel, dim3((unsigned)p.chunks, ctiles, (unsigned)slots), dim3(256), 0, s, a);
     if (p.bricks) {   // the 27-tap kernel's chunk rows hold the weight, then the bias partials (b_off = w_off + nw)
