@@ -22,6 +22,8 @@
 #include <string>
 #include <vector>
 
+#include "host_copy.h"
+
 namespace soc {
 namespace unet {
 
@@ -125,6 +127,7 @@ private:
     std::vector<uint16_t *> ha_, cat_, hd_, hqa_, hqb_, g1_, g2_, gcat_;
     uint16_t *hbot_ = nullptr;
     std::vector<void *> allocs_;
+    HostCopy host_copy_;   // parameters and gradients to the host
 };
 
 }  // namespace unet

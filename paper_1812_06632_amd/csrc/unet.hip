@@ -1236,6 +1236,7 @@ Net::Status Net::create(int dev, int32_t cin, int32_t cout, int32_t base, int32_
         for (const auto &j : jobs) max_prep_ = std::max<int64_t>(max_prep_, (int64_t)j.nph * j.npad * j.taps * j.crow);
     }
 #undef ALLOC
+    if (sizeof(float) * nparam_ >= HostCopy::kLeast) host_copy_.create();
 
     // He-normal weights, zero biases, zero optimiser state
     for (auto &L : layers_) {
@@ -1689,14 +1690,12 @@ hipError_t Net::set_params(const float *h, hipStream_t s)
 
 hipError_t Net::get_params(float *h, hipStream_t s)
 {
-    hipError_t e = hipMemcpyAsync(h, d_params_, sizeof(float) * nparam_, hipMemcpyDeviceToHost, s);
-    return e != hipSuccess ? e : hipStreamSynchronize(s);
+    return host_copy_.copy(h, d_params_, sizeof(float) * nparam_, s);
 }
 
 hipError_t Net::get_grads(float *h, hipStream_t s)
 {
-    hipError_t e = hipMemcpyAsync(h, d_grads_, sizeof(float) * nparam_, hipMemcpyDeviceToHost, s);
-    return e != hipSuccess ? e : hipStreamSynchronize(s);
+    return host_copy_.copy(h, d_grads_, sizeof(float) * nparam_, s);
 }
 
 int64_t Net::flops_forward(int32_t n) const
