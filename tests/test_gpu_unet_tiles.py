@@ -64,3 +64,17 @@ def test_between_levels(soc, base, shape):  # noqa: F811
     rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), 1, shape, 2, 2, base, 2)
     print_rows(rep)
     ctx.close()
+
+
+@pytest.mark.parametrize("cin,cout", [(1, 1), (7, 9), (17, 16)])   # channels padded to 16 and 32, 8 at a time
+def test_odd_channels(soc, cin, cout):  # noqa: F811
+    n, shape = 2, (4, 6, 10)
+    P, x, dy = _case(2, 16, n, shape, cin, cout, seed=cin)
+    ctx = soc.Context(0)
+    net = soc.UNet(ctx, cin, cout, 16, 2, n, shape)
+    net.set_params(flat(P).astype(np.float32))
+    y = net.forward(torch.from_numpy(x.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    rep = check_forward_layers(net, P, n, shape, cin, cout, 16, 2, y)
+    rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), n, shape, cin, cout, 16, 2)
+    print_rows(rep)
+    ctx.close()
