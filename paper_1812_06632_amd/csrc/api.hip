@@ -1089,7 +1089,10 @@ soc_status soc_scatter_map(soc_ctx c, soc_grid g, const soc_freq *f, const soc_s
     P.totals = c->d_peel;
     HIPCHK(c, launch_clear2((unsigned long long *)c->d_peel, 8 * kStatSlots, c->d_counter, 1, c->stream));   // totals, id pool
     const int blocks = (int)(c->num_cus * 8);
-    A.chunk = (int32_t)c->chunk;   // chunks of 64 ids measure 10% slower here (128^3, 10^6 packages)
+    // Two chunks per wave (128 of 10^6 packages: 3.36 ms at 128^3; 64 3.52, 256
+    // 3.46, 512 5.16); an octree's kernel takes whole chunks (of 64: 10% slower).
+    A.chunk = g->nlevels > 1 ? (int32_t)c->chunk
+                             : (int32_t)std::max<uint64_t>(64, std::min<uint64_t>((uint64_t)c->chunk, A.n_total / (c->num_cus * 32)));
     HIPCHK(c, launch_peel(A, P, blocks, c->stream));
     if (stats) {
         double rows[kStatSlots][8], h[6] = {};
