@@ -601,7 +601,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
 // Measured, 4 x 64^3 positions, 32 x 32 channels (58 GFLOP, 52 us at the rate
 // of a large BF16 matrix product): 110 us before (three waves of 9 taps, two
 // reads per operand, bricks along x with whole halos, dy loaded when staged),
-// 67 now; the 16 layers of a gradient of base 32, four levels 1090 and 740.
+// 64 now; the 16 layers of a gradient of base 32, four levels 1090 and 710.
 // Without the products it is 39, of which the partial sums' stores (56 MB)
 // take a third.
 constexpr int kGZ = 2, kGY = 8, kGX = 8;                 // brick
@@ -847,19 +847,23 @@ __global__ __launch_bounds__(256, 2) void wgrad3_kernel(WgradArgs a)
 #pragma unroll
         for (int q = 0; q < 6; ++q) store(acc[q], 9 * (q >> 1) + 7 + (q & 1));
     }
-    // bias partials of this chunk, after all weight partials: the 64 threads
-    // of each channel group added in order
+    // bias partials of this chunk, after all weight partials: the 16 lanes of
+    // a wave with the same channel group, then the four waves
     if (want_bias) {
-        float *const bred = reinterpret_cast<float *>(xL);   // [8][256]
-        lds_barrier();
+        float *const bred = reinterpret_cast<float *>(xL);   // [4][32]
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bred[j * kThreads + tid] = bsum[j];
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int off = 4; off < 64; off <<= 1) bsum[j] += __shfl_xor(bsum[j], off, 64);
+        lds_barrier();
+        if (lane < 4)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) bred[wave * 32 + 8 * lane + j] = bsum[j];
         lds_barrier();
         if (tid < 32 && o0 + tid < a.cout) {
-            float t = 0.0f;
-            for (int q = 0; q < kThreads / 4; ++q) t += bred[(tid & 7) * kThreads + 4 * q + (tid >> 3)];
             const size_t row = (size_t)27 * a.cin * a.cout + a.cout;   // a chunk's weight partials, then its bias partials
-            a.part[(size_t)chunk * row + (size_t)27 * a.cin * a.cout + o0 + tid] = t;
+            a.part[(size_t)chunk * row + (size_t)27 * a.cin * a.cout + o0 + tid] =
+                (bred[tid] + bred[32 + tid]) + (bred[64 + tid] + bred[96 + tid]);
         }
     }
 }
