@@ -229,8 +229,12 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_ali_kernel(McArgs A)
 // or at 0 (all waves on one frequency, the next one filling in as it
 // ends).  With Ali, a dust package's deposits in its emitting cell go to
 // the self-absorption tally, as in mc_ali_kernel.
+//
+// Three waves per SIMD (168 registers): the octree's ALI form came to 169 and
+// two waves, 44.3 ms instead of 41.4 (64^3 root cells in 3 levels, 16
+// frequencies x 10^6 packages).
 template <bool Oct, bool Ali>
-__global__ __launch_bounds__(kMcMaxBlock) void mc_multi_kernel(MultiArgs M)
+__global__ __launch_bounds__(kMcMaxBlock) __attribute__((amdgpu_waves_per_eu(3))) void mc_multi_kernel(MultiArgs M)
 {
     extern __shared__ double lds_dep[];   // [blockDim.x][kRingStride] deposits, then cells
     int32_t *lds_cell = (int32_t *)(lds_dep + kRingStride * blockDim.x);
