@@ -411,6 +411,9 @@ void soc_shg_model_destroy(soc_shg_model model);   /* valid before or after its 
  * grain count times 4 pi sigma_sk sum_i P_i B_nu_k(T_i), erg s^-1 Hz^-1 per
  * cell (0 in empty and refined cells).  d_P (device FP64
  * [ncells][S][N], optional): the populations.  Enqueued on ctx's stream.
+ * Small grids split the sizes over workgroups, with scratch of the context
+ * (a few times K x ncells doubles) that grows outside of a graph capture;
+ * without it the sizes are not split.
  * Errors: SOC_EINVAL for NULL arguments or a grid or model of another
  * context; SOC_EHIP when the launch fails. */
 soc_status soc_shg_solve(soc_ctx ctx, soc_grid grid, soc_shg_model model, const double *d_absorbed,

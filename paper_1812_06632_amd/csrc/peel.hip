@@ -16,8 +16,9 @@
 // Each lane is a small state machine: idle, transporting its package, or
 // marching a ray to the boundary (the direct light of a point source, the
 // escape depth of forced scattering, or a peel-off).  Every pass of the loop
-// takes one step of whichever it is doing, so long rays and long packages do
-// not hold the rest of the wave; idle lanes are refilled together from a
+// takes a step (on a regular grid four cells, and the rays to the observer in
+// batches) of whichever it is doing, so long rays and long packages do not
+// hold the rest of the wave; idle lanes are refilled together from a
 // wave-private id pool topped up with one atomic per `chunk` ids, as in the
 // Monte Carlo kernel.
 #include <hip/hip_runtime.h>

@@ -12,7 +12,7 @@
 // weights re-laid out (flipped taps for the 3^3 convolution, phases and taps
 // exchanged between the up and down convolutions).
 //
-// Each wave computes a 32-row x 32*NT-column tile with
+// Each wave computes 32-row x 32-column tiles with
 // v_mfma_f32_32x32x16_bf16 (8 BF16 of A and B per lane, 16 FP32 results
 // per lane); operands are 16-byte vectors per lane: 8 consecutive input
 // channels of one position of a channels-last tensor (A) and 8 consecutive
@@ -23,8 +23,9 @@
 // second gradient (the skip connection), then rounds to BF16.
 //
 // Weight gradients contract over positions: each workgroup reduces a chunk
-// of positions for one tap and a 32 x 32 (input, output channel) tile,
-// transposing the channels-last tiles through LDS, and writes a partial sum;
+// of positions for a 32 x 32 (input, output channel) tile and one tap (all 27
+// of a 3^3 layer), transposing the channels-last tiles through LDS, and writes
+// a partial sum;
 // a second kernel adds the partials in a fixed order, so training is
 // bit-reproducible.
 #include <hip/hip_runtime.h>
@@ -1096,7 +1097,7 @@ int64_t Net::positions(int level, int32_t n) const
 
 // Split-K plan of a layer's weight gradient for a batch of n: 3^3 layers
 // reduce bricks of 2 x 8 x 8 positions with all 27 taps per workgroup
-// (about 768 workgroups in all); the other kinds reduce rows per tap with
+// (about 512 workgroups in all); the other kinds reduce rows per tap with
 // the generic kernel (about 4096 workgroups).  chunks x taps x cin x cout
 // partial sums are written.
 Net::WgradPlan Net::plan_wgrad(const Layer &L, int32_t n) const
