@@ -494,6 +494,27 @@ struct WgradArgs {
 
 constexpr int kWgStep = 64;   // rows per wave and step
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// 4 positions (of row stride 32 channels) of the lane's channel, read
+// transposed from a channels-last tile; p: see tr_lane.
+__device__ inline uint2 tr_read4(const uint16_t *p)
+{
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+    return __builtin_bit_cast(uint2, v);
+}
+
+// The lane's share of a transpose read's address.
+__device__ inline int tr_lane(int lane)
+{
+    return ((lane & 15) >> 2) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+}
+
+// A wave stages its 64 rows of x and dy in LDS of its own, channels last, and
+// reads the operands transposed (see wgrad3_kernel); the next 64 rows are
+// loaded during the products.  Measured, 4 x 64^3, base 32, four levels: the six
+// layers' kernels 216 us with the operands gathered two bytes at a time between
+// two workgroup barriers, 156 now.
 __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint16_t xs[4][kWgStep][32];
@@ -515,50 +536,55 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
     const uint32_t c_begin = blockIdx.x * a.chunk;
     const uint32_t c_end = min(c_begin + a.chunk, mtot);
     const int cg = (lane & 3) * 8;
+    constexpr int kPer = kWgStep / 16;
+    const bool x_in = i0 + cg < a.x_c, d_in = o0 + cg < a.dy_c;
 
+    u32x4 vx[kPer], vd[kPer];
+    bool in[kPer];
+    const auto load = [&](uint32_t base) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const uint32_t m = base + wave * kWgStep + (lane >> 2) + 16 * j;
+            in[j] = m < c_end;
+            uint32_t t = min(m, c_end - 1);
+            const int qx = t % a.mx;
+            t /= a.mx;
+            const int qy = t % a.my;
+            t /= a.my;
+            const int qz = t % a.mz;
+            const int b = t / a.mz;
+            // (no padding: the input grid is s_in times the row grid)
+            const int zz = a.s_in * qz + tz, yy = a.s_in * qy + ty, xx = a.s_in * qx + tx;
+            vx[j] = *reinterpret_cast<const u32x4 *>(
+                a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + (x_in ? i0 + cg : 0));
+            const size_t op = (size_t)((b * a.oz + a.s_out * qz + ez) * a.oy + a.s_out * qy + ey) * a.ox + a.s_out * qx + ex;
+            vd[j] = *reinterpret_cast<const u32x4 *>(a.dy + op * a.dy_cs + a.dy_co + (d_in ? o0 + cg : 0));
+        }
+    };
     f32x16_t acc;
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-
+    const uint16_t *const xr = &xs[wave][8 * half][0] + tr_lane(lane), *const dr = &ds[wave][8 * half][0] + tr_lane(lane);
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    load(c_begin);
     for (uint32_t base = c_begin; base < c_end; base += 4 * kWgStep) {
 #pragma unroll
-        for (int j = 0; j < kWgStep / 16; ++j) {
+        for (int j = 0; j < kPer; ++j) {
             const int rr = (lane >> 2) + 16 * j;
-            const uint32_t m = base + wave * kWgStep + rr;
-            u32x4 vx = {0u, 0u, 0u, 0u}, vd = {0u, 0u, 0u, 0u};
-            if (m < c_end) {
-                uint32_t t = m;
-                const int qx = t % a.mx;
-                t /= a.mx;
-                const int qy = t % a.my;
-                t /= a.my;
-                const int qz = t % a.mz;
-                const int b = t / a.mz;
-                const int zz = a.s_in * qz + tz - a.pad, yy = a.s_in * qy + ty - a.pad, xx = a.s_in * qx + tx - a.pad;
-                if (i0 + cg < a.x_c && zz >= 0 && zz < a.iz && yy >= 0 && yy < a.iy && xx >= 0 && xx < a.ix)
-                    vx = *reinterpret_cast<const u32x4 *>(
-                        a.x + (size_t)(((b * a.iz + zz) * a.iy + yy) * a.ix + xx) * a.x_cs + a.x_co + i0 + cg);
-                if (o0 + cg < a.dy_c) {
-                    const size_t op = (size_t)((b * a.oz + a.s_out * qz + ez) * a.oy + a.s_out * qy + ey) * a.ox +
-                                      a.s_out * qx + ex;
-                    vd = *reinterpret_cast<const u32x4 *>(a.dy + op * a.dy_cs + a.dy_co + o0 + cg);
-                }
-            }
-            *reinterpret_cast<u32x4 *>(&xs[wave][rr][cg]) = vx;
-            *reinterpret_cast<u32x4 *>(&ds[wave][rr][cg]) = vd;
+            *reinterpret_cast<u32x4 *>(&xs[wave][rr][cg]) = in[j] && x_in ? vx[j] : zero;
+            *reinterpret_cast<u32x4 *>(&ds[wave][rr][cg]) = in[j] && d_in ? vd[j] : zero;
         }
-        lds_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        load(min(base + 4 * kWgStep, c_end - 1));
 #pragma unroll
-        for (int kk = 0; kk < kWgStep / 16; ++kk) {
-            u32x4 pa, pb;
-            for (int j = 0; j < 4; ++j) {
-                const int q0 = kk * 16 + 8 * half + 2 * j;
-                pa[j] = (uint32_t)xs[wave][q0][r] | ((uint32_t)xs[wave][q0 + 1][r] << 16);
-                pb[j] = (uint32_t)ds[wave][q0][r] | ((uint32_t)ds[wave][q0 + 1][r] << 16);
-            }
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pa),
-                                                          __builtin_bit_cast(bf16x8_t, pb), acc, 0, 0, 0);
+        for (int kk = 0; kk < kPer; ++kk) {
+            const uint2 a0 = tr_read4(xr + kk * 16 * 32), a1 = tr_read4(xr + (kk * 16 + 4) * 32);
+            const uint2 b0 = tr_read4(dr + kk * 16 * 32), b1 = tr_read4(dr + (kk * 16 + 4) * 32);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, u32x4{a0.x, a0.y, a1.x, a1.y}),
+                                                          __builtin_bit_cast(bf16x8_t, u32x4{b0.x, b0.y, b1.x, b1.y}), acc, 0, 0, 0);
         }
-        lds_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();   // the rows have been read
     }
     // reduce the four waves' tiles in a fixed order
     if (wave > 0)
@@ -607,22 +633,6 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
 // take a third.
 constexpr int kGZ = 2, kGY = 8, kGX = 8;                 // brick
 constexpr int kGHZ = kGZ + 2, kGHY = kGY + 2, kGHX = 12;  // halo (x padded from 10 to three reads)
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-// 4 positions (of row stride 32 channels) of the lane's channel, read
-// transposed from a channels-last tile; p: see tr_lane.
-__device__ inline uint2 tr_read4(const uint16_t *p)
-{
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-    return __builtin_bit_cast(uint2, v);
-}
-
-// The lane's share of a transpose read's address.
-__device__ inline int tr_lane(int lane)
-{
-    return ((lane & 15) >> 2) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-}
 
 // An input row: 10 positions of the lane's channel, and its x-taps.
 struct TapRow { u32x4 v; uint32_t last; };
