@@ -145,10 +145,11 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, float *tile, const
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (kF32 && !a.y) {   // FP32 output of a few channels
-        for (int i = lane; i < 32 * a.cout; i += 64) {
+    if (kF32 && !a.y) {   // FP32 output: the tile's own columns, n0 .. min(n0 + 32, cout) - 1
+        const int cols = min(32, a.cout - n0);   // (not above 0 where n0 is in the padding)
+        for (int i = lane; i < 32 * cols; i += 64) {
             size_t op;
-            if (position(i / a.cout, op)) a.yf[op * a.yf_cs + i % a.cout] = tile[(i / a.cout) * kTileRow + i % a.cout];
+            if (position(i / cols, op)) a.yf[op * a.yf_cs + n0 + i % cols] = tile[(i / cols) * kTileRow + i % cols];
         }
         return;
     }

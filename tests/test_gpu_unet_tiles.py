@@ -78,3 +78,17 @@ def test_odd_channels(soc, cin, cout):  # noqa: F811
     rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), n, shape, cin, cout, 16, 2)
     print_rows(rep)
     ctx.close()
+
+
+@pytest.mark.parametrize("cout", [31, 32, 33, 48, 64, 65, 100])   # column tiles of 32, the last one full, partial or padding
+@pytest.mark.parametrize("shape", [(3, 5, 9), (2, 128, 121)])      # one column tile per workgroup, and two
+def test_wide_outputs(soc, cout, shape):  # noqa: F811
+    P, x, dy = _case(1, 16, 1, shape, 2, cout, seed=cout)
+    ctx = soc.Context(0)
+    net = soc.UNet(ctx, 2, cout, 16, 1, 1, shape)
+    net.set_params(flat(P).astype(np.float32))
+    y = net.forward(torch.from_numpy(x.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    rep = check_forward_layers(net, P, 1, shape, 2, cout, 16, 1, y)
+    rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), 1, shape, 2, cout, 16, 1)
+    print_rows(rep)
+    ctx.close()
