@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
     const int bd = blockDim.x;
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const uint32_t iteration = __builtin_amdgcn_readfirstlane(*B.iteration);
+    const uint32_t iteration = uniform_u32(*B.iteration);
     unsigned long long n_pk = 0, n_st = 0, n_sc = 0, n_ru = 0;
     double e_em = 0.0, e_ab = 0.0, e_es = 0.0;
 
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
             const int32_t q = __builtin_amdgcn_readfirstlane(sh_item);
             if (q >= B.n_lds_items) break;
             const TileDev item = B.lds_items[q];
-            const unsigned long long id_end = __builtin_amdgcn_readfirstlane(item.end);
+            const unsigned long long id_end = uniform_u32(item.end);
             const PairDev &P = B.pairs[__builtin_amdgcn_readfirstlane(item.pair)];
             view_pair(A, P);
             const int32_t nc = (int32_t)P.ncells;
@@ -205,8 +205,8 @@ __global__ __launch_bounds__(kMcMaxBlock) void mc_batch_kernel(BatchArgs B)
             hx = P.nx >> 1;
             hy = P.ny >> 1;
             ks = P.ks_f; ka = P.ka_f; gg = P.g_f;
-            pool_next = __builtin_amdgcn_readfirstlane(tile.begin);
-            pool_end = __builtin_amdgcn_readfirstlane(tile.end);
+            pool_next = uniform_u32(tile.begin);
+            pool_end = uniform_u32(tile.end);
             continue;
         }
         const unsigned long long idle = __ballot(!active);

@@ -22,6 +22,14 @@ __device__ inline uint32_t xcd_index()
     return __builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 7u;
 }
 
+// The first lane's value in a scalar register.  (The builtin returns int: an
+// unsigned value of 2^31 or more would be extended with its sign where it
+// becomes 64 bits wide.)
+__device__ inline uint32_t uniform_u32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // Private copy (0..kPrivCopies-1) a wave adds into: its XCD and the
 // workgroup's index modulo the copies per XCD; wave-uniform.
 __device__ inline uint32_t priv_index()

@@ -77,3 +77,30 @@ def test_batch_items_cover_every_id(n_bg, lds):
         # the same FP64 deposits in another order
         np.testing.assert_allclose(A[m].cpu().numpy(), B.cpu().numpy(), rtol=1e-11)
     assert st["cell_steps"] == steps
+
+
+@pytest.mark.parametrize("n_dark", [2**31 - 500, 2**31, 2**32 - 1 - 1000])
+@pytest.mark.parametrize("lds", [0, 13824])
+def test_batch_ids_beyond_31_bits(n_dark, lds):
+    """A pair's last packages, those of a source, have ids on both sides of
+    2^31 and up to 2^32 - 2; the ids before them carry no energy (counted,
+    not traced)."""
+    from paper_1812_06632_amd import soc, workloads as W
+
+    P = W.sphere_problem(n=8, n_packages=1000)
+    ctx = soc.Context(0)
+    ctx.set_option("batch_lds_cells", lds)
+    g = soc.grid_from_workload(ctx, P.grid)
+    f = (float(P.nu[0]), float(P.w[0]), float(P.sigma_abs[0]), float(P.sigma_sca[0]), float(P.g[0]))
+    src = dict(ps_pos=[[3.5, 4.25, 4.5]], ps_Lnu=[1e20], n_ps_pk=1000)
+    A = torch.zeros(P.grid.ncells, dtype=torch.float64, device="cuda")
+    B = torch.zeros_like(A)
+    one = soc.simulate_frequency(ctx, g, f, B, seed=11, iteration=2, freq_index=0, stats=True, **src)
+    b = soc.Batch(ctx, [g], [dict(grid=0, freq=f, freq_index=0, absorbed=A, n_bg=n_dark, I_bg=0.0, **src)], seed=11)
+    st = b.run(iteration=2, stats=True)
+    assert st["packages"] == n_dark + 1000
+    for key in ("cell_steps", "scatterings", "runaways"):
+        assert st[key] == one[key], key
+    assert st["e_emitted"] == pytest.approx(one["e_emitted"], rel=1e-12, abs=0)
+    # the same FP64 deposits in another order
+    np.testing.assert_allclose(A.cpu().numpy(), B.cpu().numpy(), rtol=1e-11)
