@@ -442,7 +442,9 @@ __device__ inline int64_t leaf_lookup(const uint32_t *words, int32_t nx, int32_t
 // A ray is cut into blockDim.y parts of whole root cells (in which its
 // leaves nest): lane (x, y) integrates part y of pixel x, with its emission
 // I and its transmission E, and the parts are joined from the observer's
-// side, I_0 + E_0 (I_1 + E_1 (...)).  Bound: the latency of a cell's chain
+// side, I_0 + E_0 (I_1 + E_1 (...)).  A cell's factor of E
+// is 1 - (1 - e^{-dtau}) only while that keeps its digits: behind an opaque
+// cell it has none left, and the cell's own light may be weaker still.  Bound: the latency of a cell's chain
 // (dependent loads of the leaf's words, two FP64 exponentials); one lane per
 // ray left 256 waves for a 128^2 image: 61 us for 32^3 root cells with three
 // levels, 15 us in parts.
@@ -481,7 +483,7 @@ __global__ __launch_bounds__(kMapPixels * kMapParts) void map_kernel(MapArgs a)
                 const double S = (a.sigma_abs / a.sigma_ext) * planck_b(a.nu, (double)a.T[c]);
                 const double loss = -expm1(-dt);
                 I += S * loss * E;
-                E *= 1.0 - loss;
+                E *= dt < 0.5 ? 1.0 - loss : exp(-dt);
             }
             x = xn;
         }

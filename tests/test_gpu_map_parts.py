@@ -54,3 +54,35 @@ def test_matches_direct_sum(shape, levels, tau):
         ref = _reference(fine.astype(np.float64), Tfine.astype(np.float64), cell, 3e12, sabs, ssca, axis)
         # FP64 sums, one rounding to FP32
         np.testing.assert_allclose(img, ref, rtol=2e-7, atol=1e-12 * ref.max())
+
+
+@pytest.mark.parametrize("dt", [1e-3, 5.0, 20.0, 38.0, 60.0])
+@pytest.mark.parametrize("levels", [1, 2])
+def test_hot_cell_behind_cold_opaque_cells(dt, levels):
+    """10 K cells of depth dt each before a 300 K cell at 10 um: the light that
+    comes through is far below the depth's rounding in 1 - e^-dt, and above
+    what the cold cells emit.  One ray along each axis, from both sides."""
+    from paper_1812_06632_amd import soc
+
+    nu, cell, k = 3e13, 1e17, 2
+    ctx = soc.Context(0)
+    for axis in (0, 1, 2, 4, 5, 6):
+        shape = [1, 1, 1]
+        shape[2 - (axis & 3)] = k + 1
+        T = np.full(shape, 10.0, np.float32)
+        # the observer is on the upper side, or the lower one of axes 4 to 6
+        T.ravel()[0 if axis < 4 else -1] = 300.0
+        rho = np.ones(shape, np.float32)
+        sig = dt / cell / 2
+        G = W.regular_grid(rho, cell)
+        Tr, fine, edge = T.ravel(), T, cell
+        if levels == 2:
+            G = W.refine_all_once(G)
+            Tr = np.concatenate([np.zeros(T.size, np.float32), np.repeat(T.ravel(), 8)])
+            fine, edge = T.repeat(2, 0).repeat(2, 1).repeat(2, 2), cell / 2
+        grid = soc.grid_from_workload(ctx, G)
+        img = soc.map_image(ctx, grid, (nu, 1e11, sig, sig, 0.0), torch.from_numpy(Tr).cuda(), axis).cpu().numpy()
+        ref = _reference(np.ones(fine.shape), fine.astype(np.float64), edge, nu, sig, sig, axis)
+        # FP64 sums (each depth of at most 120 rounds by 1e-14 of itself), one rounding to FP32
+        # (the reference is rounded too: the darkest are FP32 subnormals)
+        np.testing.assert_allclose(img, ref.astype(np.float32), rtol=2e-7)
