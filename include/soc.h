@@ -411,9 +411,13 @@ void soc_shg_model_destroy(soc_shg_model model);   /* valid before or after its 
  * grain count times 4 pi sigma_sk sum_i P_i B_nu_k(T_i), erg s^-1 Hz^-1 per
  * cell (0 in empty and refined cells).  d_P (device FP64
  * [ncells][S][N], optional): the populations.  Enqueued on ctx's stream.
- * Small grids split the sizes over workgroups, with scratch of the context
- * (a few times K x ncells doubles) that grows outside of a graph capture;
- * without it the sizes are not split.
+ * Small grids (up to 16384 cells) split the sizes over workgroups, with
+ * scratch that the model was given when it was created (32768 K doubles, 34 MB
+ * for 128 bands; solves with one model on different streams wait for each
+ * other there).  The call allocates nothing.  Inside a graph capture, or with a
+ * model that got no scratch, the sizes are not split: the same result up to the
+ * order of the FP64 sum over sizes, and a graph that stays valid whatever is
+ * solved meanwhile.
  * Errors: SOC_EINVAL for NULL arguments or a grid or model of another
  * context; SOC_EHIP when the launch fails. */
 soc_status soc_shg_solve(soc_ctx ctx, soc_grid grid, soc_shg_model model, const double *d_absorbed,

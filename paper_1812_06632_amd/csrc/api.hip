@@ -60,8 +60,6 @@ struct soc_ctx_s {
     int64_t cap_priv_self = 0;
     double *d_peel = nullptr;                 // totals of a scattered-light run
     int64_t cap_peel = 0;
-    double *d_shg = nullptr;                  // emissions of the size parts of a grain solve
-    int64_t cap_shg = 0;
     double *d_L = nullptr, *d_incl = nullptr, *d_scan = nullptr;
     int64_t cap_L = 0, cap_incl = 0, cap_scan = 0;
     double *d_a = nullptr, *d_S = nullptr;   // selection weights / capped counts; sum of |L| (capped mode)
@@ -148,6 +146,11 @@ struct soc_shg_model_s {
     int32_t S = 0, K = 0, N = 0;
     double *d_buf = nullptr;   // every table in one allocation
     soc::ShgModelDev dev{};
+    // Emissions of a solve's size parts (NULL: solves take one part), made
+    // with the model, so that a solve allocates nothing.  Solves on different
+    // streams take turns with it: part_free is recorded behind each.
+    double *d_part = nullptr;
+    hipEvent_t part_free = nullptr;
 };
 
 namespace {
@@ -577,7 +580,6 @@ void soc_ctx_destroy(soc_ctx c)
     (void)hipFree(c->d_priv);
     (void)hipFree(c->d_priv_self);
     (void)hipFree(c->d_peel);
-    (void)hipFree(c->d_shg);
     (void)hipFree(c->d_L);
     (void)hipFree(c->d_incl);
     (void)hipFree(c->d_a);
@@ -1205,6 +1207,14 @@ soc_status soc_shg_model_create(soc_ctx c, int32_t K, const double *nu, const do
         delete m;
         return fail(c, SOC_EHIP, "grain model setup: %s", hipGetErrorString(e));
     }
+    // a model without the parts' scratch is a slower one on small grids, no error
+    if (const int64_t cells = shg_part_cells(S); cells > 0) {
+        if (hipEventCreateWithFlags(&m->part_free, hipEventDisableTiming) != hipSuccess) m->part_free = nullptr;
+        if (!m->part_free || hipMalloc((void **)&m->d_part, sizeof(double) * (size_t)(cells * K)) != hipSuccess) {
+            m->d_part = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     *out = m;
     return SOC_OK;
 }
@@ -1216,6 +1226,8 @@ void soc_shg_model_destroy(soc_shg_model m)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(m->device);
     (void)hipFree(m->d_buf);
+    (void)hipFree(m->d_part);
+    if (m->part_free) (void)hipEventDestroy(m->part_free);
     (void)hipSetDevice(cur);
     delete m;
 }
@@ -1238,15 +1250,27 @@ soc_status soc_shg_solve(soc_ctx c, soc_grid g, soc_shg_model m, const double *d
     a.absorbed = d_absorbed;
     a.emission = d_emission;
     a.P = d_P;
-    // the size parts' emissions need scratch; where it cannot be had (it
-    // would grow inside a graph capture, or memory is short), one part
-    int parts = shg_parts(g->ncells, m->S);
+    // A graph is replayed beside whatever else the program runs, so a captured
+    // solve (by this library or by the caller) uses no scratch: one part.
+    int parts = m->d_part ? shg_parts(g->ncells, m->S) : 1;
     if (parts > 1) {
-        const int64_t need = (int64_t)parts * m->K * g->ncells;
-        if ((c->capturing && need > c->cap_shg) || grow(c, &c->d_shg, c->cap_shg, need) != SOC_OK) parts = 1;
-        a.part = c->d_shg;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {   // the null stream beside another's capture
+            (void)hipGetLastError();
+            cs = hipStreamCaptureStatusActive;
+        }
+        if (c->capturing || cs != hipStreamCaptureStatusNone) parts = 1;
     }
-    HIPCHK(c, launch_shg(a, parts, c->stream));
+    if (parts == 1) {
+        HIPCHK(c, launch_shg(a, 1, c->stream));
+        return SOC_OK;
+    }
+    a.part = m->d_part;
+    HIPCHK(c, hipStreamWaitEvent(c->stream, m->part_free, 0));
+    const hipError_t e = launch_shg(a, parts, c->stream);
+    const hipError_t freed = hipEventRecord(m->part_free, c->stream);
+    HIPCHK(c, e);
+    HIPCHK(c, freed);
     return SOC_OK;
 }
 

@@ -520,10 +520,17 @@ __global__ __launch_bounds__(256) void shg_sum_kernel(const double *part, int pa
 // Parts the sizes are cut into: a grid of fewer than 512 tiles of 64 cells
 // (two per compute unit) leaves CUs idle, so its sizes are spread over more
 // workgroups, each with its own emission, added up afterwards.
+constexpr int64_t kShgTiles = 512;
+
 int shg_parts(int64_t ncells, int S)
 {
     const int64_t tiles = (ncells + kShgWaves * kShgCells - 1) / (kShgWaves * kShgCells);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(S, 512 / tiles));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(S, kShgTiles / tiles));
+}
+
+int64_t shg_part_cells(int S)
+{
+    return S > 1 ? kShgTiles * kShgWaves * kShgCells : 0;
 }
 
 template <int KS, int NS>

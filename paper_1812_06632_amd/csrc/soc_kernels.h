@@ -155,6 +155,7 @@ struct ShgArgs {
 };
 hipError_t launch_shg_prep(const ShgModelDev &m, const double *w, hipStream_t s);
 int shg_parts(int64_t ncells, int S);
+int64_t shg_part_cells(int S);   // the most parts x cells of any grid (0: one part always)
 // parts: size parts (1, or as a.part holds: parts x K x ncells doubles)
 hipError_t launch_shg(const ShgArgs &a, int parts, hipStream_t s);
 

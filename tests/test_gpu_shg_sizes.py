@@ -67,3 +67,86 @@ def test_cells_do_not_depend_on_their_neighbours(cells):
     np.testing.assert_array_equal(P, Pw[:cells])
     # the size parts of a small grid are added in another grouping
     np.testing.assert_allclose(E, whole[:, :cells], rtol=1e-13)
+
+
+def _line(n, G, nu, w, seed):
+    rng = np.random.default_rng(seed)
+    d = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    field = 10 ** rng.uniform(-2.0, 4.0, n)
+    A = 4 * np.pi * (W.isrf(nu) * G.sigma_per_H * w)[:, None] * (field * d * 1.0e51)[None, :]
+    return W.regular_grid(d.reshape(1, 1, n), 1.0e17), A
+
+
+@pytest.mark.parametrize("external", [False, True])
+def test_captured_solve_outlives_larger_ones(external):
+    """A graph of a small solve (sizes in parts outside of a capture) replayed
+    after larger solves and after solves of other models, with eager work and
+    synchronizations between the replays; captured by the library and by the
+    caller."""
+    from paper_1812_06632_amd import soc
+
+    nu, w = W.frequency_grid(40)
+    G = W.grain_model(nu, w, n_size=5, n_enthalpy=50)
+    G2 = W.grain_model(nu, w, n_size=9, n_enthalpy=50)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx = soc.Context(0, stream=s)
+        small, As = _line(100, G, nu, w, 1)
+        large, Al = _line(5000, G, nu, w, 2)
+        gs, gl = soc.grid_from_workload(ctx, small), soc.grid_from_workload(ctx, large)
+        m, m2 = soc.ShgModel(ctx, G), soc.ShgModel(ctx, G2)
+        As, Al = torch.from_numpy(As).cuda(), torch.from_numpy(Al).cuda()
+        want, El = torch.empty_like(As), torch.empty_like(Al)
+        soc.shg_solve(ctx, gs, m, As, want)
+        E = torch.full_like(As, -1.0)
+        if external:
+            s.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                soc.shg_solve(ctx, gs, m, As, E)
+        else:
+            soc.graph_begin(ctx)
+            soc.shg_solve(ctx, gs, m, As, E)
+            g = soc.graph_end(ctx)
+        assert torch.all(E == -1.0)   # recorded, not run
+        for k in range(4):
+            soc.shg_solve(ctx, gl, m, Al, El)
+            soc.shg_solve(ctx, gl, m2, Al, El)
+            E.fill_(-1.0)
+            (g.replay if external else g.launch)()
+            soc.shg_solve(ctx, gl, m, Al, El)
+            if k % 2:
+                s.synchronize()
+            # the sum over sizes in one part
+            np.testing.assert_allclose(E.cpu().numpy(), want.cpu().numpy(), rtol=1e-13)
+        s.synchronize()
+
+
+def test_solves_on_two_streams_take_turns():
+    """One model, two streams, nothing between the solves: the parts of one do
+    not reach the other."""
+    import ctypes
+
+    from paper_1812_06632_amd import soc
+
+    nu, w = W.frequency_grid(40)
+    G = W.grain_model(nu, w, n_size=6, n_enthalpy=50)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    ctx = soc.Context(0, stream=streams[0])
+    m = soc.ShgModel(ctx, G)
+    work = []
+    for n in (3000, 1000):
+        grid, A = _line(n, G, nu, w, n)
+        A = torch.from_numpy(A).cuda()
+        work.append((soc.grid_from_workload(ctx, grid), A, torch.empty_like(A), torch.empty_like(A)))
+    torch.cuda.synchronize()
+    for g, A, want, _ in work:
+        soc.shg_solve(ctx, g, m, A, want)
+        torch.cuda.synchronize()
+    for _ in range(20):
+        for s, (g, A, _, E) in zip(streams, work):
+            assert soc._lib.soc_ctx_set_stream(ctx.h, ctypes.c_void_p(s.cuda_stream)) == 0
+            soc.shg_solve(ctx, g, m, A, E)
+    torch.cuda.synchronize()
+    for _, _, want, E in work:
+        assert torch.equal(E, want)
