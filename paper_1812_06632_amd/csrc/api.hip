@@ -155,8 +155,11 @@ struct soc_shg_model_s {
 
 namespace {
 
+// Records a failure.  A refused allocation is not left pending in the runtime,
+// where the check of the next launch would report it once more.
 soc_status fail(soc_ctx c, soc_status s, const char *fmt, ...)
 {
+    if (s == SOC_ENOMEM) (void)hipGetLastError();
     if (c) {
         char buf[512];
         va_list ap;
