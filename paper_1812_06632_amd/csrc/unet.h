@@ -104,6 +104,7 @@ private:
     hipError_t conv_wgrad(const Layer &L, int32_t n, const View &x, const View &dy, hipStream_t s);
     struct WgradPlan {
         int64_t chunks = 0;
+        int64_t most = 0;     // chunks of any smaller batch at most
         uint32_t chunk = 0;   // bricks (3^3 layers) or rows per chunk
         bool bricks = false;
     };

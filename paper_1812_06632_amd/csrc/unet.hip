@@ -1123,6 +1123,7 @@ Net::WgradPlan Net::plan_wgrad(const Layer &L, int32_t n) const
         // (measured 4 x 64^3, base 32, four levels, with the sums of the
         // partials: 1.13 ms; 256: 1.19, 384: 1.23, 768: 1.41, 1024: 1.50)
         int64_t chunks = std::min<int64_t>(nb, std::max<int64_t>(1, 512 / ctiles));
+        p.most = chunks;
         p.chunk = (uint32_t)((nb + chunks - 1) / chunks);
         p.chunks = (nb + p.chunk - 1) / p.chunk;
         p.bricks = true;
@@ -1130,6 +1131,7 @@ Net::WgradPlan Net::plan_wgrad(const Layer &L, int32_t n) const
         const int64_t rows = L.kind == Layer::UP2 ? positions(L.level_in, n) : positions(L.level_out, n);
         const int64_t tiles = ctiles * taps_of(L.kind);
         int64_t chunks = std::min<int64_t>((rows + 1023) / 1024, std::max<int64_t>(1, 4096 / tiles));
+        p.most = chunks;
         uint32_t chunk = (uint32_t)((rows + chunks - 1) / chunks);
         p.chunk = (chunk + 255) / 256 * 256;
         p.chunks = (rows + p.chunk - 1) / p.chunk;
@@ -1269,10 +1271,11 @@ Net::Status Net::create(int dev, int32_t cin, int32_t cout, int32_t base, int32_
         }
     }
     ALLOC(hbot_, uint16_t, positions(levels - 1, nmax) * ch[levels - 1]);
-    // split-K partials: the largest chunks x taps x cin x cout of any layer
-    // (chunk counts do not decrease with the batch, so nmax bounds them)
+    // split-K partials: the largest chunks x taps x cin x cout of any layer and
+    // batch.  The chunks of a plan may be fewer with a larger batch (512 for
+    // 512 bricks, 384 of two for 768); the limit they are cut to is not.
     cap_part_ = 0;
-    for (auto &L : layers_) cap_part_ = std::max(cap_part_, plan_wgrad(L, nmax).chunks * (L.nw + L.cout));
+    for (auto &L : layers_) cap_part_ = std::max(cap_part_, plan_wgrad(L, nmax).most * (L.nw + L.cout));
     ALLOC(d_part_, float, std::max<int64_t>(cap_part_, kColBlocks * 4096));
     {
         const std::vector<PrepArgs> jobs = prep_jobs(layers_, d_params_);

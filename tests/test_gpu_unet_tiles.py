@@ -92,3 +92,27 @@ def test_wide_outputs(soc, cout, shape):  # noqa: F811
     rep += check_backward_layers(net, P, torch.from_numpy(dy.astype(np.float32)).cuda(), 1, shape, 2, cout, 16, 1)
     print_rows(rep)
     ctx.close()
+
+
+@pytest.mark.parametrize("base,levels,shape,nmax", [
+    (48, 2, (16, 16, 16), 3),   # more weight-gradient chunks for two samples than for three
+    (16, 1, (24, 24, 24), 5),   # for three and four than for five
+])
+def test_smaller_batches_than_the_network_was_made_for(soc, base, levels, shape, nmax):  # noqa: F811
+    """Every batch up to nmax gives the gradients of a network made for it."""
+    P, x, dy = _case(levels, base, nmax, shape, seed=nmax)
+    xt, dyt = (torch.from_numpy(v.astype(np.float32)).cuda() for v in (x, dy))
+    ctx = soc.Context(0)
+    large = soc.UNet(ctx, 2, 2, base, levels, nmax, shape)
+    large.set_params(flat(P).astype(np.float32))
+    for n in range(1, nmax + 1):
+        own = soc.UNet(ctx, 2, 2, base, levels, n, shape)
+        own.set_params(flat(P).astype(np.float32))
+        got = []
+        for net in (large, own):
+            y = net.forward(xt[:n].contiguous())
+            net.backward(dyt[:n].contiguous())
+            got.append((y.cpu().numpy(), net.get_grads()))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+        own.close()
+    ctx.close()
