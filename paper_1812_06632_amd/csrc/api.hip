@@ -71,6 +71,7 @@ struct soc_ctx_s {
     double *d_tmeta = nullptr;
     unsigned int *d_tfine_n = nullptr;
     double *d_tfine_T = nullptr;
+    bool temp_clear = false;             // its histograms are zero
     // soc_simulate_frequencies: per-frequency tables and argument blocks
     double *d_mL = nullptr, *d_mS = nullptr;
     int64_t cap_mL = 0, cap_mS = 0;
@@ -1403,8 +1404,9 @@ void soc_temp_table_destroy(soc_temp_table t)
     delete t;
 }
 
-// Statistics scratch of the temperature kernels (allocated and cleared on
-// first use; every call leaves the histograms zero).
+// Statistics scratch of the temperature kernels (allocated on first use).  The
+// passes leave the histograms zero for the next call, which clears them itself
+// unless the last one is known to have come to its end.
 static soc_status temp_stats_buffers(soc_ctx c, TempArgs &a)
 {
     if (!c->d_tpart) {
@@ -1426,10 +1428,13 @@ static soc_status temp_stats_buffers(soc_ctx c, TempArgs &a)
             return fail(c, SOC_ENOMEM, "temperature statistics buffers");
         }
         c->d_tpart = part;
+    }
+    if (!c->temp_clear) {
         HIPCHK(c, launch_fill_i32((int32_t *)c->d_thist, 0, kHistBins, c->stream));
         HIPCHK(c, launch_fill_i32((int32_t *)c->d_tfine_n, 0, kFineBins, c->stream));
         HIPCHK(c, launch_fill_f64(c->d_tfine_T, 0.0, kFineBins, c->stream));
     }
+    c->temp_clear = false;
     a.part = c->d_tpart;
     a.hist_total = c->d_thist;
     a.meta = c->d_tmeta;
@@ -1476,6 +1481,7 @@ static soc_status temp_stats(soc_ctx c, const TempArgs &a, soc_temp_stats *stats
 {
     HIPCHK(c, launch_temp_stats(a, c->h_tmp_out, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->temp_clear = true;
     const double *h = c->h_tmp_out;
     stats->mean_T = h[0];
     stats->hot5_mean_T = h[1];

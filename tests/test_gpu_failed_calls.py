@@ -1,5 +1,8 @@
 """Calls after one that failed: the runtime error that a refused allocation
-leaves does not reach the next."""
+leaves does not reach the next, nor does what a call had done before it
+failed."""
+import ctypes
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +41,24 @@ def test_network_that_cannot_be_had():
     assert e.value.status == soc.ENOMEM
     net = soc.UNet(ctx, 1, 1, 16, 1, 1, (4, 4, 4))
     assert torch.isfinite(net.forward(torch.ones(1, 4, 4, 4, 1, device="cuda"))).all()
+
+
+def _leave_an_error():
+    """A pending error of the HIP runtime, as a program's own refused allocation leaves it."""
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    p = ctypes.c_void_p()
+    assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(1 << 62)) != 0
+
+
+def test_temperature_statistics_after_a_failed_call():
+    soc, P, ctx, grid, f = _problem()
+    table = soc.temp_table_build(ctx, P.emit_nu, P.emit_w, P.emit_sigma_abs, P.T_floor, P.T_max, 1024)
+    T = torch.linspace(5, 50, P.grid.ncells, device="cuda")
+    want = soc.temperature_stats(ctx, grid, table, T)
+    _leave_an_error()
+    try:
+        assert soc.temperature_stats(ctx, grid, table, T) == want
+    except soc.SocError as e:
+        assert e.status == soc.EHIP
+    assert soc.temperature_stats(ctx, grid, table, T) == want
