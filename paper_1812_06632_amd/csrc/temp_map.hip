@@ -235,8 +235,10 @@ int32_t temp_blocks(int64_t ncells)
     return (int32_t)(b < 1 ? 1 : (b < kTempBlocks ? b : kTempBlocks));
 }
 
-// One workgroup's inclusive scan of one value per lane over 1024 lanes:
-// within each wave by shuffles, then over the 16 wave totals.
+// One workgroup's exclusive scan of one value per lane over 1024 lanes:
+// within each wave by shuffles, then over the 16 wave totals.  (Not the
+// inclusive scan less the lane's own value, which is no number where that is
+// infinite.)
 constexpr int kFinThreads = 1024;
 
 __device__ inline double block_scan(double v, double *sh)
@@ -252,7 +254,8 @@ __device__ inline double block_scan(double v, double *sh)
     double base = 0.0;
     for (int k = 0; k < wv; ++k) base += sh[k];
     __syncthreads();
-    return base + v;
+    const double before = __shfl_up(v, 1, 64);
+    return base + (lane > 0 ? before : 0.0);
 }
 
 // Sum over the workgroups' rows of columns col .. col + n - 1 of `part`
@@ -301,11 +304,10 @@ __global__ __launch_bounds__(kFinThreads) void temp_stats_reduce_kernel(TempArgs
         a.hist_total[hi - 1 - q] = 0u;   // left zero for the next call
         n += loc[q];
     }
-    const double upto = block_scan(n, sh_s);
+    const double before = block_scan(n, sh_s);
     const double count = sh_p[0];
     const double k = ceil(0.05 * count);
-    const double before = upto - n;
-    if (count > 0.0 && before < k && upto >= k) {
+    if (count > 0.0 && before < k && before + n >= k) {
         double cn = before;
         for (int q = 0; q < kFinPer; ++q) {
             if (cn + loc[q] >= k) {
@@ -383,13 +385,12 @@ __global__ __launch_bounds__(kFinThreads) void temp_stats_finish_kernel(TempArgs
         n += bn[q];
         sT += bT[q];
     }
-    const double upto_n = block_scan(n, sh_s), upto_T = block_scan(sT, sh_s);
+    const double before_n = block_scan(n, sh_s), before_T = block_scan(sT, sh_s);
     const double count = a.meta[0];
     const double need = a.meta[6];
     const double k = a.meta[7];
-    const double before_n = upto_n - n;
-    if (count > 0.0 && need > 0.0 && before_n < need && upto_n >= need) {
-        double cn = before_n, cT = upto_T - sT;
+    if (count > 0.0 && need > 0.0 && before_n < need && before_n + n >= need) {
+        double cn = before_n, cT = before_T;
         for (int q = 0; q < kFinePer; ++q) {
             if (cn + bn[q] >= need) {
                 cT += (need - cn) * (bT[q] / bn[q]);

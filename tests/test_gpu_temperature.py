@@ -92,3 +92,16 @@ def test_statistics_of_given_fields(field):
     st = soc.temperature_stats(ctx, grid, table, torch.from_numpy(T).cuda())
     assert st["mean_T"] == pytest.approx(T[leaf].astype(np.float64).mean(), rel=1e-12)
     assert st["hot5_mean_T"] == pytest.approx(_hot5(T[leaf]), rel=5e-7)
+
+
+@pytest.mark.parametrize("share", [0.02, 0.2, 1.0])   # above the threshold's bin, in it, everywhere
+def test_statistics_of_infinite_temperatures(share):
+    soc, W, ctx, g, grid, table, _ = _setup(23, 27, 13)
+    rng = np.random.default_rng(9)
+    T = rng.uniform(5.0, 30.0, g.ncells).astype(np.float32)
+    T[rng.random(g.ncells) < share] = np.inf
+    st = soc.temperature_stats(ctx, grid, table, torch.from_numpy(T).cuda())
+    assert st["mean_T"] == np.inf and st["hot5_mean_T"] == np.inf
+    T[~np.isfinite(T)] = 20.0   # nothing of it is left in the next call
+    st = soc.temperature_stats(ctx, grid, table, torch.from_numpy(T).cuda())
+    assert st["hot5_mean_T"] == pytest.approx(_hot5(T[g.density() > 0]), rel=5e-7)
