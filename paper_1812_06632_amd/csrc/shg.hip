@@ -357,7 +357,10 @@ __global__ __launch_bounds__(64 * kShgWaves, 1) void shg_kernel(ShgArgs a)
             cnt[t] = m.count[(int64_t)s * N + t];
         }
         // suffix sums of the photon rates: each lane sums its bands on top of the later lanes'
-        {
+        if (!(m.abundance[s] > 0.0)) {   // no grains: no photons, whatever the cell absorbs (it may be no number)
+#pragma unroll
+            for (int i = 0; i < KB; ++i) SR[(k0 + i) * kShgCells + cell] = 0.0;
+        } else {
             const double *g = m.rate + (int64_t)s * (8 * KS) + k0;   // 0 from K on
             double tot = 0.0;
 #pragma unroll

@@ -150,3 +150,35 @@ def test_solves_on_two_streams_take_turns():
     torch.cuda.synchronize()
     for _, _, want, E in work:
         assert torch.equal(E, want)
+
+
+@pytest.mark.parametrize("absorbed", [np.nan, np.inf])
+def test_sizes_without_grains_absorb_nothing(absorbed):
+    """Whatever the field: their grains stay in the lowest bin and emit
+    nothing, and the other cells of the wave are not touched."""
+    from paper_1812_06632_amd import soc
+
+    nu, w = W.frequency_grid(40)
+    G = W.grain_model(nu, w, n_size=3, n_enthalpy=50)
+    grid, A = _line(40, G, nu, w, 3)
+    A[7, 5] = absorbed
+
+    def solve():   # (as _solve, whose comparison of two solves takes no NaN)
+        ctx = soc.Context(0)
+        Ad = torch.from_numpy(A).cuda()
+        E = torch.full_like(Ad, -1.0)
+        P = torch.full((grid.ncells, 3, 50), -1.0, dtype=torch.float64, device="cuda")
+        soc.shg_solve(ctx, soc.grid_from_workload(ctx, grid), soc.ShgModel(ctx, G), Ad, E, P)
+        return E.cpu().numpy(), P.cpu().numpy()
+
+    G.abundance[1] = 0.0
+    E, P = solve()
+    assert not np.isfinite(E[:, 5]).any() and not np.isfinite(P[5, [0, 2]]).any()   # two sizes have grains
+    np.testing.assert_array_equal(P[:, 1, 0], 1.0)
+    assert not P[:, 1, 1:].any()
+    others = np.arange(40) != 5
+    assert np.isfinite(E[:, others]).all() and np.isfinite(P[others]).all()
+    G.abundance[:] = 0.0
+    E, P = solve()
+    assert not E.any()
+    np.testing.assert_array_equal(P[:, :, 0], 1.0)
