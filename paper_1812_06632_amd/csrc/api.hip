@@ -101,7 +101,7 @@ struct soc_batch_s {
     PairDev *d_pairs = nullptr;
     TileDev *d_tiles = nullptr;
     PsArg *d_ps = nullptr;
-    unsigned int *d_counter = nullptr;      // [0] next tile, [1] next LDS pair
+    unsigned int *d_counter = nullptr;      // [0] next tile, [1] next LDS item
     uint32_t *d_iteration = nullptr;
     TileDev *d_lds_items = nullptr;         // pairs of small grids or parts of them, largest cost first
     int32_t n_lds_items = 0;
@@ -1782,7 +1782,8 @@ BatchLaunch batch_launch(soc_ctx c, bool lds, int64_t lds_cells)
 {
     if (!lds) return BatchLaunch{(int)(c->num_cus * c->blocks_per_cu), (int)c->block};
     // a workgroup holds a small grid's tally: 512-lane workgroups, as many
-    // per compute unit as their LDS allows (at most two)
+    // per compute unit as their LDS allows (at most two; the kernel's 195
+    // registers leave room for the 8 waves of one at a time)
     const int64_t ring = (int64_t)kRingStride * kMcMaxBlock * (int64_t)(sizeof(double) + sizeof(int32_t));
     const int64_t need = std::max<int64_t>(ring, lds_cells * (int64_t)sizeof(double)) + 256;
     const int64_t per_cu = std::min<int64_t>(2, std::max<int64_t>(1, c->lds_per_cu / need));

@@ -299,7 +299,8 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a, int32_t phases)
 // operand read from LDS for one product, weights in rows, two-byte epilogue),
 // 0.34 ms now.  What is left is the latency of a chunk on the small grids (a
 // wave per SIMD or less) and, on the large ones, the halo loads between two
-// barriers with two waves per SIMD.
+// barriers with two waves per SIMD, whose 256 registers are all taken (three
+// are spilled in the form with two column tiles).
 constexpr int kH3 = 10;                       // halo edge in y and x
 constexpr int kRow3 = kH3 * 16 + 8;           // 168 elements per halo row: an odd number of 16-byte units
 
